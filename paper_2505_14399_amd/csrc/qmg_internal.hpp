@@ -346,6 +346,10 @@ void set_dslash_variant(int v);
 void launch_dslash(qmg_prec prec, const void* U, const void* in, void* out, const DslashArgs& a,
                    hipStream_t st);
 
+// the same on fields in the canonical layouts (a.canonical; launch_dslash comes here by itself)
+void launch_dslash_canonical(qmg_prec prec, const void* U, const void* in, void* out, const DslashArgs& a,
+                             hipStream_t st);
+
 // layout conversion (canonical FP64 <-> native storage), spinors and gauge
 // canonical [nrhs][V][12] in precision pc <-> native [nrhs][12][V] in precision pn
 void launch_pack_spinor(const void* canon, qmg_prec pc, void* native, qmg_prec pn, int V, int nrhs, hipStream_t st);

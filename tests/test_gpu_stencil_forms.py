@@ -1,0 +1,42 @@
+"""The stencil forms that only some sizes reach: canonical-layout tiles (remainders, groups of
+right-hand sides, 16-byte and unaligned fields, 16-bit storage) against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import fields
+from oracle import wilson
+from tests._util import to_gpu, to_np, rel, banner
+
+pytestmark = pytest.mark.gpu
+
+# a result is a sum of about 40 products: single precision to 40 roundings of 2^-24, 16-bit
+# storage to the rounding of the result (2^-9, bf16; 2^-12, f16), double to 40 * 2^-53
+TOL = {"f64": 1e-14, "f32": 2.4e-6, "bf16": 3e-3, "f16": 4e-4}
+REAL = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def _store(a, prec, shift):
+    """The array in storage type prec (16-bit: trailing pairs), its first number `shift` numbers
+    into its allocation; and its values in double precision."""
+    t = torch.view_as_real(to_gpu(a)).to(REAL[prec])
+    vals = to_np(torch.view_as_complex(t.double()))
+    buf = torch.zeros(t.numel() + 2 * shift, dtype=t.dtype, device="cuda")
+    buf[2 * shift:] = t.reshape(-1)
+    t = buf[2 * shift:].view(t.shape)
+    return (torch.view_as_complex(t) if prec in ("f64", "f32") else t), vals
+
+
+@pytest.mark.parametrize("dims", [(1, 3, 2, 2), (4, 4, 4, 4), (5, 3, 7, 3), (16, 6, 5, 4), (3, 70, 1, 2)])
+@pytest.mark.parametrize("prec,nrhs,shift", [("f64", 1, 0), ("f64", 5, 0), ("f32", 1, 0), ("f32", 4, 0), ("f32", 3, 1),
+                                             ("bf16", 2, 0), ("f16", 1, 0), ("bf16", 3, 1)])
+@pytest.mark.parametrize("dag", [False, True])
+def test_canonical_forms(qmg, dims, prec, nrhs, shift, dag):
+    banner(f"canonical forms {dims} {prec} nrhs={nrhs} shift={shift} dag={dag}")
+    U, Uv = _store(fields.random_gauge(dims, 0.6, 91), prec, shift)
+    psi, pv = _store(fields.gaussian_spinor(dims, nrhs, 92), prec, shift)
+    lat = qmg.Lattice(dims, 0.07, 2.5, -1)
+    out = (qmg.wilson_apply_adj if dag else qmg.wilson_apply)(lat, U, psi)
+    got = to_np(out if out.is_complex() else torch.view_as_complex(out.double()))
+    ref = (wilson.apply_wilson_adj if dag else wilson.apply_wilson)(Uv, pv, 0.07, 2.5, -1, dims)
+    assert rel(got, ref) < TOL[prec]
