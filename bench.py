@@ -57,7 +57,7 @@ FAMILY_KERNEL = {
     "restrict": ("k_restrict", "transfer.hip"),
     "prolong": ("k_prolong", "transfer.hip"),
     "coarse_build": ("k_build_coarse", "transfer.hip"),
-    "evenodd/hop": ("k_hop_eo", "hop.hip"),
+    "evenodd/hop": ("k_hop_", "hop_pair.hip"),
     "coarse_eo": ("k_coarse_eo_apply", "coarse_evenodd.hip"),
     "sstep/gram": ("k_sstep_gram", "evenodd.hip"),
     "blas/axpby": ("k_axpby<", "krylov.hip"),

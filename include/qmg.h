@@ -382,7 +382,8 @@ qmg_status qmg_mg_set_cycle(qmg_mg* mg, int32_t coarse_steps, int32_t graph);
  *   site term and its inverse are built once (FP64, and in the inner precision when that is
  *   not FP64) from the handle's fields; when every link is SU(3) to 1e-12 (third row = complex
  *   conjugate of the cross product of the first two) only the first two rows are stored and
- *   the hop kernels rebuild the third.  Synchronizes the stream.  Works with every form of
+ *   the hop kernels rebuild the third (an FP32 copy of 2^18 sites or more with Lx a multiple of 4
+ *   keeps all three).  Synchronizes the stream.  Works with every form of
  *   qmg_mg_set_cycle.  The choice is not stored by qmg_mg_save.
  * Errors: EINVAL (null, eo not 0/1/2), ESHAPE (an odd extent), EBREAKDOWN (a singular site
  *   block), ENOMEM, EHIP. */

@@ -297,11 +297,11 @@ struct KCycle : Precond {
     const size_t nf = size_t(nrhs) * 12 * h.g.V, nh = nf / 2;
     eo_t.ensure(nf * sizeof(S));
     for (DevBuf* b : {&eo_e, &eo_o, &eo_u, &eo_b, &eo_xe, &eo_xo}) b->ensure(nh * sizeof(S));
-    if (!schur) schur.reset(new SchurOp(h.g, p, h.Ueo[w].p, h.Aeo[w].p, h.Aieo[w].p, false, h.eo_ne));
+    if (!schur) schur.reset(new SchurOp(h.g, p, h.Ueo[w].p, h.Aeo[w].p, h.Aieo[w].p, false, h.eo_ne[w]));
     D.apply(z_s, eo_t.p, nrhs, st);
     launch_eo_split_sub(p, h.g, r_s, eo_t.p, eo_e.p, eo_o.p, nrhs, st);  // t = r - D z by parity
     DslashArgs a = make_dslash_args(h.g, nrhs, false, false);
-    a.link_ne = h.eo_ne;
+    a.link_ne = h.eo_ne[w];
     launch_site_eo(p, a, schur->Aio, true, eo_o.p, eo_u.p, st);
     const int ns = std::max(1, h.n_post);
     const bool sstep = h.eo_smoother == 2 && ns <= 8;
@@ -1919,14 +1919,18 @@ qmg_status qmg_mg_set_smoother(qmg_mg* mg, int32_t eo, hipStream_t stream) {
     const size_t n = size_t(36) * g.V;
     if (!h.Ueo[0].p) {
       // SU(3) links (to 1e-12) are stored as their first two rows: the hop kernels rebuild the
-      // third, and read two thirds of the link bytes
-      h.eo_ne = launch_su3_row_defect(g, h.U64.p, stream) < 1e-12 ? 6 : 9;
+      // third, and read two thirds of the link bytes.  An FP32 copy keeps all three where the hop
+      // takes two sites per thread from one right-hand side on: that form reads a link's columns
+      // one after another, and two rows of two sites do not fit its registers (225 spilled)
+      h.eo_ne[0] = launch_su3_row_defect(g, h.U64.p, stream) < 1e-12 ? 6 : 9;
+      const bool pair = h.inner == QMG_F32 && g.L[0] % 4 == 0 && g.V >= kHopPairSites;
+      h.eo_ne[1] = pair ? 9 : h.eo_ne[0];
     }
     for (int w = 0; w < (h.inner != QMG_F64 ? 2 : 1); ++w) {
       const qmg_prec p = w ? h.inner : QMG_F64;
       if (!h.Ueo[w].p) {
-        h.Ueo[w].alloc(size_t(4) * h.eo_ne * g.V * prec_bytes(p));
-        launch_eo_gauge_from_native(g, h.U64.p, h.Ueo[w].p, p, stream, h.eo_ne);
+        h.Ueo[w].alloc(size_t(4) * h.eo_ne[w] * g.V * prec_bytes(p));
+        launch_eo_gauge_from_native(g, h.U64.p, h.Ueo[w].p, p, stream, h.eo_ne[w]);
       }
       if (h.A64.p && !h.Aeo[w].p) {
         h.Aeo[w].alloc(n * prec_bytes(p));

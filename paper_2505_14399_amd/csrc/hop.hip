@@ -322,6 +322,8 @@ void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const voi
   // The same holds for BF16/FP16 storage (BF16 at 16^3 x 32: Wilson 8.7 against 17.8 us, clover
   // 21.0 against 18.5 us; the forms tie at 24^3 x 64).
   const bool with_site_term = (ym == 2 && Ap) || (post == 1 && Aip);
+  // FP32 without a forced variant: two sites per thread where its rule holds
+  const bool pair = prec == QMG_F32 && a.tchunk == 0 && hop_pair_fits(a, Ue, Uo, in, y, out, Ap, Aip);
   const bool split =
       a.tchunk == 16 || (a.tchunk != 1 && with_site_term && long(Vh) * a.nrhs < (1L << 19));
   const int per_wg = split ? kBlock / 4 : kBlock;
@@ -330,7 +332,11 @@ void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const voi
   // right-hand sides per thread of the one-site-per-thread form: forced with the launch-variant
   // codes 501 .. 504, else HOP_NR (FP32 storage and below) once there are enough of them
   int nr = 1;
-  if (!split) {
+  if (pair) {
+    // two right-hand sides per thread halve the link loads, but also the waves (16^3 x 32, us, one
+    // against two: 4 rhs 60 / 67, 8 rhs 103 / 91; 32^3 x 64: 4 rhs 926 / 813)
+    nr = a.nrhs >= 2 && long(a.V) * a.nrhs >= (1L << 20) ? 2 : 1;
+  } else if (!split) {
     if (a.tchunk >= 501 && a.tchunk <= 504) nr = a.tchunk - 500;
     else if (prec != QMG_F64 && a.nrhs >= 2) nr = std::min(a.nrhs, kHopNR);
   }
@@ -354,6 +360,13 @@ void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const voi
   // as one (events on the stream around both) rather than the first launch alone
   const bool two = nr > 1 && a.nrhs >= nr && a.nrhs % nr != 0;
   TimedLaunch tl("evenodd/hop", st, bytes, 1320.0 * Vh * a.nrhs, !two);
+  QMG_CHECK((ym == 0 && post == 1) || (ym == 2 && post == 0) || (ym == 1 && post == 0) || (ym == 1 && post == 1),
+            QMG_EINVAL, "even-odd hop form (%d, %d) is not built", ym, post);
+  if (pair) {
+    launch_hop_pair(a, Ue, Uo, p, in, y, out, Ap, Aip, ym, post, sgn, nr, st);
+    QMG_LAUNCH_CHECK();
+    return;
+  }
   auto go = [&](auto tag) {
     using S = decltype(tag);
     auto run = [&](auto kern) {
@@ -410,8 +423,6 @@ void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const voi
       else pick(std::false_type{}, N9{});
     }
   };
-  QMG_CHECK((ym == 0 && post == 1) || (ym == 2 && post == 0) || (ym == 1 && post == 0) || (ym == 1 && post == 1),
-            QMG_EINVAL, "even-odd hop form (%d, %d) is not built", ym, post);
   switch (prec) {
     case QMG_F64: go(double2{}); break;
     case QMG_F32: go(float2{}); break;

@@ -369,6 +369,15 @@ void launch_clover_field(const Geom& g, const void* U64, double cs, double ct, v
 void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const void* Uo, int p, const void* in,
                    const void* y, void* out, const void* Ap, const void* Aip, int ym, int post, double sgn,
                    hipStream_t st);
+// the same in FP32 storage with two sites per thread (hop_pair.hip; launch_hop_eo goes there by
+// itself): Lx a multiple of 4, whole links, every pointer 16-byte aligned, planes of less than 4 GB,
+// enough sites; nr: right-hand sides per thread, 1 or 2
+constexpr long kHopPairSites = 1L << 18;  // sites x right-hand sides from which it is the faster form
+bool hop_pair_fits(const DslashArgs& a, const void* Ue, const void* Uo, const void* in, const void* y,
+                   const void* out, const void* Ap, const void* Aip);
+void launch_hop_pair(const DslashArgs& a, const void* Ue, const void* Uo, int p, const void* in, const void* y,
+                     void* out, const void* Ap, const void* Aip, int ym, int post, double sgn, int nr,
+                     hipStream_t st);
 // out = M in (M = A_p, or A_p^-1 with inv) on one parity's half fields
 void launch_site_eo(qmg_prec prec, const DslashArgs& a, const void* M, bool inv, const void* in, void* out,
                     hipStream_t st);

@@ -1,5 +1,6 @@
 """The stencil forms that only some sizes reach: canonical-layout tiles (remainders, groups of
-right-hand sides, 16-byte and unaligned fields, 16-bit storage) against the oracle."""
+right-hand sides, 16-byte and unaligned fields, 16-bit storage) against the oracle, and the
+two-sites-per-thread even-odd hop against the double-precision operator."""
 import numpy as np
 import pytest
 import torch
@@ -40,3 +41,29 @@ def test_canonical_forms(qmg, dims, prec, nrhs, shift, dag):
     got = to_np(out if out.is_complex() else torch.view_as_complex(out.double()))
     ref = (wilson.apply_wilson_adj if dag else wilson.apply_wilson)(Uv, pv, 0.07, 2.5, -1, dims)
     assert rel(got, ref) < TOL[prec]
+
+
+# every extent even, Lx a multiple of 4, 2^18 sites x right-hand sides or more; patches of 8, 4 and 2
+# planes, rows of one pair, an odd right-hand side behind groups of two
+PAIRS = [((4, 16, 64, 64), 1, False), ((12, 16, 44, 34), 1, True), ((16, 16, 32, 64), 3, False),
+         ((20, 22, 18, 10), 4, True), ((8, 8, 10, 12), 40, False)]
+
+
+@pytest.mark.parametrize("dims,nrhs,clov", PAIRS)
+@pytest.mark.parametrize("dag", [False, True])
+def test_hop_pairs(qmg, dims, nrhs, clov, dag):
+    banner(f"even-odd hop, two sites per thread {dims} nrhs={nrhs} clover={clov} dag={dag}")
+    V = int(np.prod(dims))
+    assert V * nrhs >= 1 << 18
+    g = torch.Generator(device="cuda").manual_seed(7)
+    m = torch.view_as_complex(torch.randn(256, 3, 3, 2, generator=g, device="cuda", dtype=torch.float64))
+    q = torch.linalg.qr(m.cpu())[0].cuda()  # unitary links
+    U = q[torch.randint(0, 256, (4, V), generator=g, device="cuda")].contiguous()
+    psi = torch.view_as_complex(torch.randn(nrhs, V, 4, 3, 2, generator=g, device="cuda", dtype=torch.float64))
+    lat = qmg.Lattice(dims, 0.1, 2.0, -1)
+    out = {}
+    for prec in ("f32", "f64"):
+        A, Ai = qmg.eo_site_term(lat, U, 0.9, 1.1, prec) if clov else (None, None)
+        e, _ = qmg.eo_pack_spinor(lat, psi, prec)
+        out[prec] = to_np(qmg.schur_apply(lat, qmg.eo_pack_gauge(lat, U, prec), e, A, Ai, dagger=dag))
+    assert rel(out["f32"], out["f64"]) < 4 * TOL["f32"]  # two hops and their site terms, inputs rounded to 2^-24
