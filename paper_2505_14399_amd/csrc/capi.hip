@@ -1642,11 +1642,7 @@ qmg_status qmg_prolong(const qmg_mg* mg, const void* coarse_in, void* fine_out, 
     QMG_CHECK(prec == QMG_F64 || (prec == h.inner && prec == QMG_F32), QMG_EDTYPE,
               "prolong: precision must be F64 or the F32 inner precision");
     const void* P = prec == QMG_F64 ? h.P64.p : h.Pin.p;
-    const size_t n = size_t(nrhs) * 12 * h.g.V;
-    DevBuf nat(n * prec_bytes(prec));
-    launch_prolong(prec, h, P, coarse_in, nat.p, nrhs, stream);
-    launch_unpack_spinor(nat.p, prec, fine_out, prec, h.g.V, nrhs, stream);
-    QMG_HIP(hipStreamSynchronize(stream));
+    launch_prolong(prec, h, P, coarse_in, fine_out, nrhs, stream, true);
   });
 }
 
@@ -1661,11 +1657,7 @@ qmg_status qmg_restrict(const qmg_mg* mg, const void* fine_in, void* coarse_out,
     QMG_CHECK(prec == QMG_F64 || (prec == h.inner && prec == QMG_F32), QMG_EDTYPE,
               "restrict: precision must be F64 or the F32 inner precision");
     const void* P = prec == QMG_F64 ? h.P64.p : h.Pin.p;
-    const size_t n = size_t(nrhs) * 12 * h.g.V;
-    DevBuf nat(n * prec_bytes(prec));
-    launch_pack_spinor(fine_in, prec, nat.p, prec, h.g.V, nrhs, stream);
-    launch_restrict(prec, h, P, nat.p, coarse_out, nrhs, stream);
-    QMG_HIP(hipStreamSynchronize(stream));
+    launch_restrict(prec, h, P, fine_in, coarse_out, nrhs, stream, true);
   });
 }
 

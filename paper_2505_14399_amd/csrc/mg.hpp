@@ -92,12 +92,32 @@ inline StencilRef stencil_above(const HierarchyDev& h, size_t i) {
   return s;
 }
 
-// prolong: fine[rhs] (native, storage S) = P coarse[rhs]
+// the number of a fine vector: component comp (3 spin + colour) of site of right-hand side r
+template <bool CANON>
+__device__ inline size_t fine_idx(int r, int comp, int site, int V) {
+  return CANON ? (size_t(r) * V + site) * 12 + comp : (size_t(r) * 12 + comp) * V + site;
+}
+// XCD-local index of workgroup b of nb: the hardware deals workgroups to the eight XCDs round
+// robin (b % 8), so this numbering gives each XCD one contiguous range.  The transfers use it
+// so that neighbouring aggregates, whose blocks share cache lines of the fine vectors (4 sites
+// of a 128-byte line of 16 in FP32), run on one XCD and meet those lines in its L2.
+__device__ inline int xcd_local(int b, int nb) {
+  const int q = nb >> 3, rem = nb & 7, x = b & 7, i = b >> 3;
+  return x * q + min(x, rem) + i;
+}
+
+// prolong: fine[rhs] (native, or canonical; storage S) = P coarse[rhs]
 void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const void* coarse, void* fine, int nrhs,
-                    hipStream_t st);
+                    hipStream_t st, bool canonical = false);
 // restrict: coarse[rhs] = P^dag fine[rhs]
 void launch_restrict(qmg_prec prec, const HierarchyDev& h, const void* P, const void* fine, void* coarse, int nrhs,
-                     hipStream_t st);
+                     hipStream_t st, bool canonical = false);
+// the same on the matrix cores (transfer_mm.hip), for the block shapes and counts that fit
+bool transfer_mm_fits(const HierarchyDev& h, int nrhs);
+void launch_prolong_mm(qmg_prec prec, const HierarchyDev& h, const void* P, const void* coarse, void* fine, int nrhs,
+                       bool canonical, hipStream_t st);
+void launch_restrict_mm(qmg_prec prec, const HierarchyDev& h, const void* P, const void* fine, void* coarse, int nrhs,
+                        bool canonical, hipStream_t st);
 // out = D_c in, coarse vectors [nrhs][d][2k]
 void launch_coarse_apply(qmg_prec prec, const HierarchyDev& h, const void* Y, const void* in, void* out, int nrhs,
                          hipStream_t st, const int* skip = nullptr);  // skip: device early-exit flag

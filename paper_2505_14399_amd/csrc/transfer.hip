@@ -13,22 +13,13 @@ namespace {
 
 inline unsigned cdiv(size_t a, size_t b) { return unsigned((a + b - 1) / b); }
 
-// XCD-local index of workgroup b of nb: the hardware deals workgroups to the eight XCDs round
-// robin (b % 8), so this numbering gives each XCD one contiguous range.  The transfers use it
-// so that neighbouring aggregates, whose blocks share cache lines of the fine vectors (4 sites
-// of a 128-byte line of 16 in FP32), run on one XCD and meet those lines in its L2.
-__device__ inline int xcd_local(int b, int nb) {
-  const int q = nb >> 3, rem = nb & 7, x = b & 7, i = b >> 3;
-  return x * q + min(x, rem) + i;
-}
-
 // ---------------------------------------------------------------------------------------
 // prolong: one thread per pack of PR rows of a (j, alpha) block, for NR right-hand sides; the
 // k coarse coefficients of those right-hand sides are staged in LDS, so P is read once per
 // group of right-hand sides.  Rows are s6 * nd + ib; the fine site is bsite[j][ib].
 // Grid: one dimension of npack * 2d * groups workgroups, in XCD-local order (row packs of a
 // block, then the blocks, then the groups of right-hand sides).
-template <class S, int PR, int NR>
+template <class S, int PR, int NR, bool CANON>
 __global__ __launch_bounds__(256) void k_prolong(const S* __restrict__ P, const S* __restrict__ vc,
                                                  S* __restrict__ fine, const int* __restrict__ bsite, int nd, int N,
                                                  int k, int d, int V, int nrhs, int npack) {
@@ -85,7 +76,7 @@ __global__ __launch_bounds__(256) void k_prolong(const S* __restrict__ P, const 
     const int comp = 6 * a + s6;
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r < nr) stc(fine, (size_t(rhs0 + r) * 12 + comp) * V + site, acc[r][u]);
+      if (r < nr) stc(fine, fine_idx<CANON>(rhs0 + r, comp, site, V), acc[r][u]);
   }
 }
 
@@ -93,7 +84,7 @@ __global__ __launch_bounds__(256) void k_prolong(const S* __restrict__ P, const 
 // vector is gathered into LDS; thread t takes row packs t, t + 256, ... and accumulates
 // conj(P) psi for eight columns at a time, which are then summed over the workgroup (wavefront
 // shuffles, then LDS across the four wavefronts).  P is read once per group.
-template <class S, int PR, int NR>
+template <class S, int PR, int NR, bool CANON>
 __global__ __launch_bounds__(256) void k_restrict(const S* __restrict__ P, const S* __restrict__ fine,
                                                   S* __restrict__ vc, const int* __restrict__ bsite, int nd, int N,
                                                   int k, int d, int V, int nrhs) {
@@ -110,14 +101,18 @@ __global__ __launch_bounds__(256) void k_restrict(const S* __restrict__ P, const
   // pass rather than two per element)
   constexpr int GU = 6;
   for (int base = 0; base < N; base += 256 * GU) {
+    // canonical vectors: a site's six components next to each other, native: its sites
     size_t off[GU];
+    int at[GU];
 #pragma unroll
     for (int u = 0; u < GU; ++u) {
       const int row = base + u * 256 + threadIdx.x;
       off[u] = 0;
+      at[u] = 0;
       if (row < N) {
-        const int s6 = row / nd, ib = row - s6 * nd;
-        off[u] = size_t(6 * a + s6) * V + bsite[size_t(j) * nd + ib];
+        const int s6 = CANON ? row % 6 : row / nd, ib = CANON ? row / 6 : row - s6 * nd;
+        off[u] = fine_idx<CANON>(0, 6 * a + s6, bsite[size_t(j) * nd + ib], V);
+        at[u] = s6 * nd + ib;
       }
     }
 #pragma unroll
@@ -126,7 +121,7 @@ __global__ __launch_bounds__(256) void k_restrict(const S* __restrict__ P, const
       if (row < N) {
 #pragma unroll
         for (int r = 0; r < NR; ++r)
-          psi[size_t(r) * N + row] = r < nr ? ldc(fine, size_t(rhs0 + r) * 12 * V + off[u]) : cplx<C>{C(0), C(0)};
+          psi[size_t(r) * N + at[u]] = r < nr ? ldc(fine, size_t(rhs0 + r) * 12 * V + off[u]) : cplx<C>{C(0), C(0)};
       }
     }
   }
@@ -919,10 +914,11 @@ static int row_pack(int N) {
 }
 
 void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const void* coarse, void* fine, int nrhs,
-                    hipStream_t st) {
+                    hipStream_t st, bool canonical) {
   TimedLaunch tl("prolong", st, double(h.g.V) * (12.0 * h.k + 12.0 * nrhs) * prec_bytes(prec),
                  8.0 * 12.0 * h.k * h.g.V * nrhs);
   QMG_CHECK(h.k <= 64, QMG_EINVAL, "prolong: rank above 64");
+  if (transfer_mm_fits(h, nrhs)) return launch_prolong_mm(prec, h, P, coarse, fine, nrhs, canonical, st);
   dispatch_prec(prec, [&](auto tag) {
     using S = decltype(tag);
     constexpr int PK = kPack<S>;
@@ -932,8 +928,12 @@ void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const v
       const int npack = int(cdiv(h.blk.N / PR, 256));
       const size_t nwg = size_t(npack) * 2 * h.blk.d * cdiv(nrhs, NR);
       QMG_CHECK(nwg < (size_t(1) << 31), QMG_EINVAL, "prolong: grid too large");
-      launch(k_prolong<S, PR, NR>, dim3(unsigned(nwg)), dim3(256), 0, st, P, coarse, fine, h.bsite.as<int>(),
-             h.blk.nd, h.blk.N, h.k, h.blk.d, h.g.V, nrhs, npack);
+      auto run = [&](auto kern) {
+        launch(kern, dim3(unsigned(nwg)), dim3(256), 0, st, P, coarse, fine, h.bsite.as<int>(), h.blk.nd, h.blk.N,
+               h.k, h.blk.d, h.g.V, nrhs, npack);
+      };
+      if (canonical) run(k_prolong<S, PR, NR, true>);
+      else run(k_prolong<S, PR, NR, false>);
     };
     using one = std::integral_constant<int, 1>;
     using four = std::integral_constant<int, 4>;
@@ -952,9 +952,10 @@ void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const v
 }
 
 void launch_restrict(qmg_prec prec, const HierarchyDev& h, const void* P, const void* fine, void* coarse, int nrhs,
-                     hipStream_t st) {
+                     hipStream_t st, bool canonical) {
   TimedLaunch tl("restrict", st, double(h.g.V) * (12.0 * h.k + 12.0 * nrhs) * prec_bytes(prec),
                  8.0 * 12.0 * h.k * h.g.V * nrhs);
+  if (transfer_mm_fits(h, nrhs)) return launch_restrict_mm(prec, h, P, fine, coarse, nrhs, canonical, st);
   dispatch_prec(prec, [&](auto tag) {
     using S = decltype(tag);
     constexpr int PK = kPack<S>;
@@ -963,8 +964,12 @@ void launch_restrict(qmg_prec prec, const HierarchyDev& h, const void* P, const 
       constexpr int PR = decltype(pr)::value, NR = decltype(nrt)::value;
       const size_t lds = size_t(NR) * h.blk.N * sizeof(cplx<ctype<S>>);
       QMG_CHECK(lds <= 96 * 1024, QMG_EINVAL, "restrict: aggregate too large for LDS staging");
-      launch(k_restrict<S, PR, NR>, dim3(2 * h.blk.d, cdiv(nrhs, NR)), dim3(256), uint32_t(lds), st, P, fine,
-             coarse, h.bsite.as<int>(), h.blk.nd, h.blk.N, h.k, h.blk.d, h.g.V, nrhs);
+      auto run = [&](auto kern) {
+        launch(kern, dim3(2 * h.blk.d, cdiv(nrhs, NR)), dim3(256), uint32_t(lds), st, P, fine, coarse,
+               h.bsite.as<int>(), h.blk.nd, h.blk.N, h.k, h.blk.d, h.g.V, nrhs);
+      };
+      if (canonical) run(k_restrict<S, PR, NR, true>);
+      else run(k_restrict<S, PR, NR, false>);
     };
     using one = std::integral_constant<int, 1>;
     using four = std::integral_constant<int, 4>;
