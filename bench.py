@@ -53,6 +53,7 @@ FAMILY_KERNEL = {
     "dslash/dir": ("k_dslash_dir", "dslash.hip"),
     "dslash/site": ("k_dslash<", "dslash.hip"),
     "dslash/twalk": ("k_dslash_t<", "dslash.hip"),
+    "dslash/pair": ("k_dslash_pair<", "dslash_pair.hip"),
     "coarse_apply": ("k_coarse_apply", "transfer.hip"),
     "restrict": ("k_restrict", "transfer.hip"),
     "prolong": ("k_prolong", "transfer.hip"),
@@ -62,10 +63,10 @@ FAMILY_KERNEL = {
     "sstep/gram": ("k_sstep_gram", "evenodd.hip"),
     "blas/axpby": ("k_axpby<", "krylov.hip"),
     "blas/axpy_multi": ("k_axpy_multi", "krylov.hip"),
-    "batch/dslash": ("k_dslash_padded", "dslash.hip"),
+    "batch/dslash": ("k_dslash_pair_padded", "dslash_pair.hip"),
     "batch/coarse_build": ("k_b_galerkin", "batch.hip"),
 }
-FAMILIES = ("dslash/site", "dslash/twalk", "dslash/dir", "isvd", "coarse_apply", "prolong", "restrict",
+FAMILIES = ("dslash/site", "dslash/twalk", "dslash/pair", "dslash/dir", "isvd", "coarse_apply", "prolong", "restrict",
             "coarse_build", "evenodd/hop", "coarse_eo")
 CLOVER_FAMILIES = tuple(f.replace("dslash/", "clover/") for f in FAMILIES)
 CLOVER_WORKLOAD = "aniso16x32_clover"

@@ -484,7 +484,7 @@ void qmg_batch_destroy(qmg_batch* b);
  * launch of each kernel family and then about one in n (picked by a hash of the call index)
  * with a pair of HIP events attached to the dispatch (its own start and end).  Every
  * kernel of the library belongs to a family: the operators ("dslash/site", "dslash/twalk",
- * "dslash/dir", "dslash/canonical", "dslash/batched", "clover/...", "evenodd/hop",
+ * "dslash/dir", "dslash/pair", "dslash/canonical", "dslash/batched", "clover/...", "evenodd/hop",
  * "coarse_apply", "coarse_eo", "prolong", "restrict", "level_..."), the Krylov vector kernels
  * ("blas/mdot_norm", "blas/axpy_scale", "blas/axpy_multi", ..., "krylov/givens", "sstep/..."),
  * the setup ("setup/philox", "setup/gather", "isvd/...", "coarse_build", ...), layout

@@ -316,7 +316,9 @@ struct BatchOp : LinOp {
     const int nr = ncol / b.nl;
     double sites = 0;
     for (int v : b.V) sites += v;
-    launch_dslash_padded(p, lat, b.nl, nr, b.Vpad, U, in, out, false, sites * (24.0 * nr + 36.0) * prec_bytes(p),
+    bool even_rows = true;
+    for (const Geom& g : b.geo) even_rows = even_rows && g.L[0] % 2 == 0;
+    launch_dslash_padded(p, lat, b.nl, nr, b.Vpad, even_rows, U, in, out, false, sites * (24.0 * nr + 36.0) * prec_bytes(p),
                          1368.0 * sites * nr, st);
   }
   size_t len() const override { return b.fine_len(); }

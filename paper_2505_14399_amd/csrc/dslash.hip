@@ -335,15 +335,31 @@ __global__ __launch_bounds__(kBlock) void k_dslash_t(const S* __restrict__ U, co
 // spinor components 3w .. 3w+2 of the 64 sites.  Four times as many threads as the site
 // kernel, each with two hops in flight: for lattices too small to fill the GPU with one
 // thread per site.
+//
+// bzt (BZ | BT << 8, or 0): where planes hold whole tiles, the tiles of BZ x BT planes (z, t) are visited
+// together (t fastest, then z, then the tiles of a plane), so that the slices a tile's t-hops read are
+// read by tiles running close in time.
 template <class S, bool DAG, bool CLOV = false>
 __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, const S* __restrict__ in,
-                                                       S* __restrict__ out, DslashArgs a) {
+                                                       S* __restrict__ out, DslashArgs a, int bzt) {
   using C = ctype<S>;
   constexpr int TS = kBlock / 4;  // sites per workgroup
   __shared__ cplx<C> part[4][12][TS];
   const int wg = xcd_tile(blockIdx.x, gridDim.x);
   const int ntile = (a.V + TS - 1) / TS;
-  const int tile = wg % ntile, rhs = wg / ntile;
+  int tile = wg % ntile;
+  const int rhs = wg / ntile;
+  if (bzt) {
+    const int BZ = bzt & 0xff, BT = bzt >> 8, tpp = (a.L[0] * a.L[1]) / TS;
+    const int h = tile % tpp;
+    int r = tile / tpp;
+    const int tt = r % BT;
+    r /= BT;
+    const int zz = r % BZ;
+    r /= BZ;
+    const int nbz = a.L[2] / BZ;
+    tile = h + tpp * ((r % nbz) * BZ + zz + a.L[2] * ((r / nbz) * BT + tt));
+  }
   const int lane = threadIdx.x & (TS - 1), mu = threadIdx.x / TS;
   const int site = tile * TS + lane;
   const bool live = site < a.V;
@@ -437,15 +453,19 @@ __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, 
 template <class S>
 void launch_dir(const void* U, const void* in, void* out, const DslashArgs& a, hipStream_t st) {
   dim3 grid(unsigned((a.V + kBlock / 4 - 1) / (kBlock / 4)) * unsigned(a.nrhs));
+  // FP64 visits patches of 4 x 4 planes (16^3 x 32, one rhs: 30.2 -> 26.3 us; 24^3 x 64 106 -> 105); the
+  // narrower types, whose planes are smaller against the L2, lose by it (BF16 16^3 x 32: 10.0 -> 11.8)
+  auto patch = [](int L) { return L % 4 == 0 ? 4 : L % 2 == 0 ? 2 : 1; };
+  const bool whole = (a.L[0] * a.L[1]) % (kBlock / 4) == 0;
+  const int bzt = whole && sizeof(S) == 16 ? patch(a.L[2]) | (patch(a.L[3]) << 8) : 0;
+  auto go = [&](auto kern) { launch(kern, grid, dim3(kBlock), 0, st, U, in, out, a, bzt); };
   if (a.clov) {
-    if (a.dagger)
-      launch(k_dslash_dir<S, true, true>, grid, dim3(kBlock), 0, st, U, in, out, a);
-    else
-      launch(k_dslash_dir<S, false, true>, grid, dim3(kBlock), 0, st, U, in, out, a);
+    if (a.dagger) go(k_dslash_dir<S, true, true>);
+    else go(k_dslash_dir<S, false, true>);
   } else if (a.dagger) {
-    launch(k_dslash_dir<S, true>, grid, dim3(kBlock), 0, st, U, in, out, a);
+    go(k_dslash_dir<S, true>);
   } else {
-    launch(k_dslash_dir<S, false>, grid, dim3(kBlock), 0, st, U, in, out, a);
+    go(k_dslash_dir<S, false>);
   }
   QMG_LAUNCH_CHECK();
 }
@@ -520,6 +540,10 @@ void run_twx(int v, const void* U, const void* in, void* out, const DslashArgs& 
   }
 }
 
+// launch codes of the two-sites-per-thread form (dslash_pair.hip) with 1 or 2 right-hand sides per
+// thread; chosen by the heuristic or the autotuner
+constexpr int kPair1 = 9001, kPair2 = 9002;
+
 template <class S>
 void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hipStream_t st) {
   const bool clov = a.clov != nullptr;
@@ -546,9 +570,9 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
   auto run = [&](int v) {
     const int cm = v / 10000;  // 10000 + code: the t-walks in t-chunk-major workgroup order
     v %= 10000;
-    const int f = v == 16 ? 0 : (v == 1 || v == 32 || v == 64) ? 1 : 2;
-    static const char* const fams[2][3] = {{"dslash/dir", "dslash/site", "dslash/twalk"},
-                                           {"clover/dir", "clover/site", "clover/twalk"}};
+    const int f = v > 9000 ? 3 : v == 16 ? 0 : (v == 1 || v == 32 || v == 64) ? 1 : 2;
+    static const char* const fams[2][4] = {{"dslash/dir", "dslash/site", "dslash/twalk", "dslash/pair"},
+                                           {"clover/dir", "clover/site", "clover/twalk", "clover/pair"}};
     TimedLaunch tl(fams[clov ? 1 : 0][f], st, bytes, flops);
     switch (v) {
       case 8: launch_tw<S, 8, 1>(U, in, out, a, 0, st, cm); break;
@@ -557,13 +581,17 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
       case 16: launch_dir<S>(U, in, out, a, st); break;
       case 32: launch_t<S, 2>(U, in, out, a, st); break;
       case 64: launch_t<S, 4>(U, in, out, a, st); break;
+      case kPair1: launch_dslash_pair(U, in, out, a, 1, st); break;
+      case kPair2: launch_dslash_pair(U, in, out, a, 2, st); break;
       default:
         if (v > 100) run_twx<S>(v, U, in, out, a, st, cm);
         else launch_t<S, 1>(U, in, out, a, st);
         break;
     }
   };
+  const bool pairs = sizeof(S) == 8 && dslash_pair_fits(a, U, in, out);
   auto valid = [&](int v) {
+    if (v == kPair1 || v == kPair2) return pairs && a.nrhs >= v - 9000;
     if (v >= 10000) {
       v -= 10000;
       if (v < 2 || v == 16 || v == 32 || v == 64 || v >= 10000) return false;
@@ -598,11 +626,25 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
     const int z = (a.L[0] * a.L[1]) % kBlock == 0 ? 1 : 0;
     const int tch = (nr == 3 && Lt % 8 == 0) ? 8 : Lt % 4 == 0 ? 4 : 2;
     if (nr && valid(1000 * z + 100 * nr + tch)) choice = 1000 * z + 100 * nr + tch;
+    // too few sites for that: the direction split (clover, us, against the t-walk: 12^4 with 4 rhs 15.5 /
+    // 81, 12 rhs 35 / 107; 16^3 x 32 with 4 rhs 72 / 83, with 8 rhs 144 / 131)
+    if (long(a.V) * a.nrhs <= (1L << 19)) choice = 16;
   }
+  // Two sites per thread.  Against them the t-walks carry neighbours from step to step, and win where
+  // there are sites enough (Wilson, us, t-walk / pairs: 32^3 x 64 with 1 rhs 261 / 276, 2 rhs 423 / 440;
+  // 24^3 x 64 with 8 rhs 616 / 644; 24^3 x 48 with 4 rhs 264 / 261); below, and with the clover term for
+  // several right-hand sides everywhere, the pairs' 16-byte loads do (16^3 x 32 with 1 rhs 16.0 / 14.8, 4 rhs
+  // 47 / 37, 8 rhs 82 / 74, 12 rhs 127 / 105; 24^3 x 48 with 1 rhs 88 / 69; clover 16^3 x 32 with 4 rhs 83 / 49,
+  // 32^3 x 64 with 4 rhs 1186 / 937, 12 rhs 2994 / 2704, 1 rhs 413 / 420).  Below 2^17 sites x rhs half
+  // the threads are too few (18 x 5 x 9 x 13, 3 rhs: 9.0 / 10.0).
+  const long work = long(a.V) * a.nrhs;
+  if (pairs && work >= (1L << 17) && (work < (1L << 21) || (clov && a.nrhs > 1)))
+    choice = a.nrhs > 1 && work >= (1L << 20) ? kPair2 : kPair1;
   // t-walks in t-chunk-major order: every XCD works on the same t-chunk, so the neighbour
   // re-reads that miss an XCD's L2 meet the chunk in the last-level cache (measured at
   // 32^3x64: 4 rhs 824 -> 773 us, 1 and 12 rhs within 2-4%)
-  if ((choice == 2 || choice == 4 || choice == 8 || choice > 100) && valid(10000 + choice)) choice += 10000;
+  if ((choice == 2 || choice == 4 || choice == 8 || (choice > 100 && choice < 9000)) && valid(10000 + choice))
+    choice += 10000;
   if (tune_enabled()) {
     const std::string key = "dslash/" + std::to_string(int(StoreTraits<S>::prec)) + "/" + std::to_string(a.L[0]) +
                             "x" + std::to_string(a.L[1]) + "x" + std::to_string(a.L[2]) + "x" +
@@ -610,9 +652,11 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
                             (clov ? "/clover" : "");
     const int cached = tune_lookup(key);
     if (cached > 0) {
-      choice = cached;
+      if (valid(cached)) choice = cached;  // the pairs' form also asks for aligned fields
     } else {
-      int cand[48], n = 0;
+      int cand[50], n = 0;
+      for (int v : {kPair1, kPair2})
+        if (valid(v)) cand[n++] = v;
       for (int v : {1, 16, 2, 4, 8, 32, 64, 202, 204, 208, 302, 304, 308, 1202, 1204, 1208, 1302, 1304, 1308})
         for (int c : {0, 10000})
           if ((c == 0 || (v != 1 && v != 16 && v != 32 && v != 64)) && valid(c + v)) cand[n++] = c + v;
@@ -644,9 +688,12 @@ void launch_dslash_batched(qmg_prec prec, const BatchLattice* lat_dev, int n_lat
   QMG_LAUNCH_CHECK();
 }
 
-void launch_dslash_padded(qmg_prec prec, const BatchLattice* lat_dev, int nl, int nr, int Vpad, const void* U,
-                          const void* in, void* out, bool dagger, double bytes, double flops, hipStream_t st) {
+void launch_dslash_padded(qmg_prec prec, const BatchLattice* lat_dev, int nl, int nr, int Vpad, bool even_rows,
+                          const void* U, const void* in, void* out, bool dagger, double bytes, double flops,
+                          hipStream_t st) {
   TimedLaunch tl("batch/dslash", st, bytes, flops);
+  // FP32 with every row of even length: two sites per thread
+  if (prec == QMG_F32 && even_rows) return launch_dslash_pair_padded(lat_dev, nl, nr, Vpad, U, in, out, dagger, st);
   const int ntile = (Vpad + kBlock - 1) / kBlock;
   auto go = [&](auto tag) {
     using S = decltype(tag);

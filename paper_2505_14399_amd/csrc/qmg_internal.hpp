@@ -338,14 +338,22 @@ void launch_dslash_batched(qmg_prec prec, const BatchLattice* lat_dev, int n_lat
                            const void* const* U, const void* const* in, void* const* out, bool dagger,
                            double bytes, double flops, hipStream_t st);
 // many lattices in padded layouts (see k_dslash_padded): nl lattices of nr spinors each
-void launch_dslash_padded(qmg_prec prec, const BatchLattice* lat_dev, int nl, int nr, int Vpad, const void* U,
-                          const void* in, void* out, bool dagger, double bytes, double flops, hipStream_t st);
+// even_rows: every lattice's Lx is even
+void launch_dslash_padded(qmg_prec prec, const BatchLattice* lat_dev, int nl, int nr, int Vpad, bool even_rows,
+                          const void* U, const void* in, void* out, bool dagger, double bytes, double flops,
+                          hipStream_t st);
 void set_dslash_variant(int v);
 
 // out = D in (or D^dag) ; U in the same storage type and layout as the spinors
 void launch_dslash(qmg_prec prec, const void* U, const void* in, void* out, const DslashArgs& a,
                    hipStream_t st);
 
+// two neighbouring sites per thread in FP32 storage (dslash_pair.hip): Lx even, pointers 16-byte
+// aligned, planes of less than 4 GB; nr: right-hand sides per thread, 1 or 2
+bool dslash_pair_fits(const DslashArgs& a, const void* U, const void* in, const void* out);
+void launch_dslash_pair(const void* U, const void* in, void* out, const DslashArgs& a, int nr, hipStream_t st);
+void launch_dslash_pair_padded(const BatchLattice* lat, int nl, int nr, int Vpad, const void* U, const void* in,
+                               void* out, bool dagger, hipStream_t st);
 // the same on fields in the canonical layouts (a.canonical; launch_dslash comes here by itself)
 void launch_dslash_canonical(qmg_prec prec, const void* U, const void* in, void* out, const DslashArgs& a,
                              hipStream_t st);

@@ -1,6 +1,6 @@
 """The stencil forms that only some sizes reach: canonical-layout tiles (remainders, groups of
 right-hand sides, 16-byte and unaligned fields, 16-bit storage) against the oracle, and the
-two-sites-per-thread even-odd hop against the double-precision operator."""
+two-sites-per-thread stencils against the double-precision operator."""
 import numpy as np
 import pytest
 import torch
@@ -67,3 +67,36 @@ def test_hop_pairs(qmg, dims, nrhs, clov, dag):
         e, _ = qmg.eo_pack_spinor(lat, psi, prec)
         out[prec] = to_np(qmg.schur_apply(lat, qmg.eo_pack_gauge(lat, U, prec), e, A, Ai, dagger=dag))
     assert rel(out["f32"], out["f64"]) < 4 * TOL["f32"]  # two hops and their site terms, inputs rounded to 2^-24
+
+
+# Lx even, 2^17 sites x right-hand sides or more (two right-hand sides per thread from 2^20 on): rows of one
+# pair, odd extents, a last tile that is not full, an odd right-hand side behind groups of two; and
+# fields off 16 bytes, which take another form
+DPAIRS = [((2, 63, 32, 33), 1, False), ((6, 17, 37, 36), 1, True), ((10, 9, 13, 8), 16, False),
+          ((14, 16, 17, 31), 9, True), ((16, 12, 18, 30), 11, False)]
+
+
+@pytest.mark.parametrize("dims,nrhs,clov", DPAIRS)
+@pytest.mark.parametrize("dag", [False, True])
+def test_dslash_pairs(qmg, dims, nrhs, clov, dag):
+    banner(f"dslash, two sites per thread {dims} nrhs={nrhs} clover={clov} dag={dag}")
+    V = int(np.prod(dims))
+    assert V * nrhs >= 1 << 17
+    g = torch.Generator(device="cuda").manual_seed(8)
+    U = torch.view_as_complex(torch.randn(4, V, 3, 3, 2, generator=g, device="cuda", dtype=torch.float64))
+    psi = torch.view_as_complex(torch.randn(nrhs, V, 4, 3, 2, generator=g, device="cuda", dtype=torch.float64))
+    lat = qmg.Lattice(dims, 0.1, 2.0, -1)
+    out = {}
+    for prec, shift in (("f64", 0), ("f32", 0), ("f32", 1)):
+        Un, p = qmg.pack_gauge(lat, U, prec), qmg.pack_spinor(lat, psi, prec)
+        buf = torch.empty(p.numel() + shift, dtype=p.dtype, device="cuda")
+        buf[shift:] = p.reshape(-1)
+        p = buf[shift:].view(p.shape)
+        if clov:
+            A = qmg.clover_field(lat, U, 0.9, 1.1, prec)
+            r = qmg.clover_apply(lat, Un, A, p, layout="native", dagger=dag)
+        else:
+            r = (qmg.wilson_apply_adj if dag else qmg.wilson_apply)(lat, Un, p, layout="native")
+        out[prec, shift] = to_np(r)
+    for shift in (0, 1):
+        assert rel(out["f32", shift], out["f64", 0]) < 2 * TOL["f32"]  # inputs rounded to 2^-24 as well
