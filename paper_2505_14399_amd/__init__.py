@@ -154,25 +154,39 @@ def _check(rc):
         raise QmgError(rc, _lib.qmg_last_error().decode())
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without the Stream object around it (on the smallest calls, whose
+    # kernels take 3 us, the caller's side is what a call costs)
+    if _raw_stream is not None and _raw_device is not None:
+        torch.cuda._lazy_init()
+        return _raw_stream(_raw_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
+def _addr(t: torch.Tensor) -> int:
+    """Address of a contiguous GPU tensor."""
     if not t.is_cuda:
         raise ValueError("tensor must be on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptr(t: Optional[torch.Tensor]):
+    return None if t is None else ctypes.c_void_p(_addr(t))
+
+
+_COMPLEX = {torch.complex128: F64, torch.complex64: F32}
 
 
 def _prec_of(t: torch.Tensor) -> int:
-    if t.dtype == torch.complex128:
-        return F64
-    if t.dtype == torch.complex64:
-        return F32
+    p = _COMPLEX.get(t.dtype)
+    if p is not None:
+        return p
     if t.dtype == torch.bfloat16 and t.shape[-1] == 2:
         return BF16
     if t.dtype == torch.float16 and t.shape[-1] == 2:
@@ -206,15 +220,17 @@ class Lattice:
 
 
 def _apply(fn, lat, U, psi, layout, out):
-    lib = load_library()
+    lib = _lib or load_library()
     prec = _prec_of(psi)
     if _prec_of(U) != prec:
         raise TypeError("U and psi must have the same precision")
     nrhs = psi.shape[0]
     out = torch.empty_like(psi) if out is None else out
     s = lat.c()
-    _check(getattr(lib, fn)(ctypes.byref(s), _ptr(U), _ptr(psi), _ptr(out), nrhs, prec,
-                            CANONICAL if layout == "canonical" else NATIVE, _stream()))
+    rc = getattr(lib, fn)(ctypes.byref(s), _addr(U), _addr(psi), _addr(out), nrhs, prec,
+                          CANONICAL if layout == "canonical" else NATIVE, _stream())
+    if rc:
+        _check(rc)
     return out
 
 
