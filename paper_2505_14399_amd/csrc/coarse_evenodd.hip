@@ -135,7 +135,8 @@ __global__ __launch_bounds__(256) void k_coarse_eo_blocks(const double2* __restr
   if (tid == 0) atomicMax(reinterpret_cast<unsigned long long*>(flag + 2), omax);
 }
 
-// One colour of the even-odd coarse operator (the form in the file header).  One workgroup per
+// One colour of the even-odd coarse operator (the form in the file header) on few right-hand sides (more
+// go to the matrix cores).  One workgroup per
 // (aggregate of the colour, group of NR right-hand sides); the staged inputs and the column
 // chunking over H follow the full coarse apply: thread (h, slot, row pack) forms PR rows of
 // B_slot(j) times its input over column chunk h, the partial rows are summed in LDS.  Slots
@@ -371,6 +372,10 @@ void launch_coarse_eo_apply(qmg_prec prec, const HierarchyDev& h, int colour, co
              static_cast<const S*>(y), static_cast<const S*>(a), static_cast<const S*>(b), static_cast<S*>(out), list,
              nbh, dh, m, nrhs, H, lo, ns, sgn);
     };
+    if (coarse_mm_fits(h.k, nrhs)) {
+      launch_coarse_mm<S>({B, y, a, b, out, list, nbh, sgn}, dh, h.k, nrhs, st);
+      return;
+    }
     if (m % PK == 0) {
       if (nrhs >= 3) go(k_coarse_eo_apply<S, 4, PK>, 4, PK);
       else if (nrhs == 2) go(k_coarse_eo_apply<S, 2, PK>, 2, PK);

@@ -124,6 +124,19 @@ void launch_coarse_apply(qmg_prec prec, const HierarchyDev& h, const void* Y, co
 // the same for any nine-block stencil: d sites, 2k dof per site, neighbour table cnb [d][8]
 void launch_stencil_apply(qmg_prec prec, int d, int k, const int* cnb, const void* Y, const void* in, void* out,
                           int nrhs, hipStream_t st, const int* skip = nullptr);
+// one colour or all of the nine-block stencil on several right-hand sides, on the matrix cores
+// (coarse_mm.hip): out(h) = [y(h)] + [Y_0(j) a(h)] + sgn sum_{s=1..8} Y_s(j) b(nb[j][s - 1]), j = list[h]
+// (or h), vectors of d aggregates; without a or b (nullptr) their slots are left out.  S: double2, float2,
+// cbf16, chalf.
+struct CoarseMm {
+  const void *Y, *y, *a, *b;
+  void* out;
+  const int *list, *nb;
+  double sgn;
+};
+bool coarse_mm_fits(int k, int nrhs);
+template <class S>
+void launch_coarse_mm(const CoarseMm& c, int d, int k, int nrhs, hipStream_t st, const int* skip = nullptr);
 // third level: Philox coarse test vectors [n][d][m] FP64 (counter (j, g, v0 + n, level))
 void launch_philox_coarse(uint64_t seed, int v0, int n, int d, int m, int level, void* out, hipStream_t st);
 // chiral split of r coarse vectors [r][d1][2k1] FP64 into blocks [2d][r][N] FP64

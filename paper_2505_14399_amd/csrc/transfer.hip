@@ -185,7 +185,8 @@ __global__ __launch_bounds__(256) void k_restrict(const S* __restrict__ P, const
   }
 }
 
-// coarse apply: one workgroup per (aggregate, group of NR right-hand sides).  The nine input
+// coarse apply on one or two right-hand sides (four above rank 24; more go to the matrix cores): one
+// workgroup per (aggregate, group of NR right-hand sides).  The nine input
 // vectors v(j + slot) are staged in LDS.  Thread (h, slot, row pack) forms PR rows of
 // Y_slot(j) times v(j + slot) over column chunk h of H (each Y entry read once per group of
 // right-hand sides; PR consecutive rows of a column-major block are one 16-byte load); the
@@ -1010,6 +1011,10 @@ void launch_stencil_apply(qmg_prec prec, int d, int k, const int* cnb, const voi
       launch(kern, dim3(d, (nrhs + NR - 1) / NR), dim3(threads), uint32_t(lds), st, Y, in, out, cnb, d, m, nrhs, H,
              skip);
     };
+    if (coarse_mm_fits(k, nrhs)) {
+      launch_coarse_mm<S>({Y, nullptr, in, in, out, nullptr, cnb, 1.0}, d, k, nrhs, st, skip);
+      return;
+    }
     const bool packed = m % PK == 0;
     if (packed) {
       if (nrhs >= 3) go(k_coarse_apply<S, 4, PK>, 4, PK);

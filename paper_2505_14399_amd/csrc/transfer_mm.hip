@@ -15,24 +15,13 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "mfma.hpp"
 #include "mg.hpp"
 #include "timing.hpp"
 
 namespace qmg {
 
 namespace {
-
-template <class C> struct Mm;
-template <> struct Mm<float> {
-  typedef float V4 __attribute__((ext_vector_type(4)));
-  __device__ static V4 mul(float a, float b, V4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lane, int v) { return 4 * (lane >> 4) + v; }  // of element v of the result
-};
-template <> struct Mm<double> {
-  typedef double V4 __attribute__((ext_vector_type(4)));
-  __device__ static V4 mul(double a, double b, V4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lane, int v) { return (lane >> 4) + 4 * v; }
-};
 
 constexpr int kMmSites = 1024;  // largest block
 
@@ -124,7 +113,8 @@ __global__ __launch_bounds__(256) void k_prolong_mm(const S* __restrict__ P, con
             const C got = dpp_move<0xB1, 0xF>(send);  // quad_perm [1,0,3,2]
             const cplx<C> o = im ? cplx<C>{got, acc[1][nt][v]} : cplx<C>{acc[0][nt][v], got};
             const int lo = 32 * q + 2 * M::row(lane, v) + (im ? 1 : 0), so = lo / IB, io = lo % IB;
-            if (r < R) buf[CANON ? (r * IB + io) * 12 + 6 * al + so : (r * 12 + 6 * al + so) * IB + io] = StoreTraits<S>::st(o);
+            if (r < R)
+              buf[CANON ? (r * IB + io) * 12 + 6 * al + so : (r * 12 + 6 * al + so) * IB + io] = StoreTraits<S>::st(o);
           }
         }
       }
