@@ -4,6 +4,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "mfma.hpp"
 #include "mg.hpp"
 #include "timing.hpp"
 
@@ -261,10 +262,10 @@ struct BuildArgs {
 
 __device__ inline int lex4(const int* c, const int* L) { return c[0] + L[0] * (c[1] + L[1] * (c[2] + L[2] * c[3])); }
 
-// chi (12 comps, chirality beta only) -> H chi  for direction dir with link u (already U or U^dag)
+// chi (12 comps, chirality beta only) -> H chi (components m apart)  for direction dir with link u (already U or U^dag)
 template <int MU>
 __device__ inline void hop_col(const cplx<double>* q, int beta, double sg, const cplx<double>* u, double coef,
-                               cplx<double>* out) {
+                               cplx<double>* out, int m) {
   // h = chi_up + sg A chi_dn
   cplx<double> h[6];
   for (int c = 0; c < 3; ++c) {
@@ -279,128 +280,163 @@ __device__ inline void hop_col(const cplx<double>* q, int beta, double sg, const
     else if (MU == 2) { h[c] = u0 + sg * times_mi(d0); h[3 + c] = u1 + sg * times_i(d1); }
     else { h[c] = u0 + sg * d0; h[3 + c] = u1 + sg * d1; }
   }
-  cplx<double> w[6];
-  for (int sp = 0; sp < 2; ++sp)
-    for (int a = 0; a < 3; ++a) {
-      cplx<double> t = {0, 0};
-      for (int bb = 0; bb < 3; ++bb) t += u[3 * a + bb] * h[3 * sp + bb];
-      w[3 * sp + a] = t;
-    }
+#pragma unroll
   for (int c = 0; c < 3; ++c) {
-    cplx<double> w0 = w[c], w1 = w[3 + c];
-    out[c] = coef * w0;
-    out[3 + c] = coef * w1;
+    cplx<double> w0{0, 0}, w1{0, 0};
+#pragma unroll
+    for (int bb = 0; bb < 3; ++bb) {
+      const cplx<double> v = u[3 * c + bb];
+      w0 += v * h[bb];
+      w1 += v * h[3 + bb];
+    }
+    out[c * m] = coef * w0;
+    out[(3 + c) * m] = coef * w1;
     cplx<double> l0, l1;
     if (MU == 0) { l0 = times_i(w1); l1 = times_i(w0); }
     else if (MU == 1) { l0 = w1; l1 = -w0; }
     else if (MU == 2) { l0 = times_i(w0); l1 = times_mi(w1); }
     else { l0 = w0; l1 = w1; }
-    out[6 + c] = (coef * sg) * l0;
-    out[9 + c] = (coef * sg) * l1;
+    out[(6 + c) * m] = (coef * sg) * l0;
+    out[(9 + c) * m] = (coef * sg) * l1;
   }
 }
 
 constexpr int kMaxM = 64;        // 2k <= 64
 
-// grid (d, 8): workgroup (j, dir) forms, for the hops of direction dir leaving the sites of
+// grid (d, 4): workgroup (j, dir) forms, for the hops of direction dir leaving the sites of
 // aggregate j, the sum over sites of P_j(x)^dag H(x, dir) P_{j'}(x + dir) as a small GEMM:
 // rows (alpha, i) of P_j(x)^dag, columns (beta, l) of H P at the neighbour, reduction over
 // the sites and the 6 spin-colour components of chirality alpha.  The sites of the block are
 // visited by class from a host-built list: hops that stay inside the block (accumulated into
 // the partial W[dir][j] of Y_0), then, for dir 0 only, the diagonal term (m+1+3/xi) P^dag P
 // (also into W), then the hops through the face (written to Y_{1+dir}(j)).  NS sites are
-// staged per phase; each thread owns a TS x TS tile of the (2k) x (2k) block.
-template <int TS>
-__global__ __launch_bounds__(256) void k_build_coarse(const double2* __restrict__ U, const double2* __restrict__ P,
-                                                      const int* __restrict__ bsite, const int* __restrict__ lists,
-                                                      double2* __restrict__ Y, double2* __restrict__ W, BuildArgs a,
-                                                      int NS) {
+// staged per phase, whose numbers are fetched while the phase before is multiplied.
+//
+// The products run on the matrix cores on what lies in the LDS as it is: real and imaginary parts of P and
+// H P count as rows (2k of a chirality) and columns (4k) of one real product, a wavefront forms RT x RT of
+// its 16 x 16 tiles, and the four real products of a complex one are put together at the end.  With a tile
+// of 3 x 3 complex numbers per thread instead, six 16-byte LDS reads for 36 multiply-adds, and the loads of
+// a phase waited for in turn, the LDS and the waits set the time.  Measured (whole coarse phase of the setup,
+// rank 24): 32^3 x 64 73.3 -> 48.4 ms (67.9 with the loads ahead alone), 16^3 x 32 4.80 -> 3.17 ms, 8^3 x 16
+// 1.28 -> 0.75 ms; rank 8 at 16^3 x 32 2.27 -> 0.89 ms.  What is left is the hop itself (a thread per column
+// of P, FP64 on the vector units), with two workgroups per CU by their registers and LDS.
+template <int RT>
+__global__ __launch_bounds__(256, 2) void k_build_coarse(const double2* __restrict__ U, const double2* __restrict__ P,
+                                                         const int* __restrict__ bsite, const int* __restrict__ lists,
+                                                         double2* __restrict__ Y, double2* __restrict__ W, BuildArgs a,
+                                                         int NS) {
   extern __shared__ unsigned char smem_raw[];
   const int k = a.k, m = 2 * k, N = a.N, nd = a.nd, V = a.V;
   cplx<double>* Px = reinterpret_cast<cplx<double>*>(smem_raw);  // [NS][12][k]
   cplx<double>* HP = Px + size_t(NS) * 12 * k;                    // [NS][12][m]
   cplx<double>* lnk = HP + size_t(NS) * 12 * m;                   // [NS][9]
-  double* scoef = reinterpret_cast<double*>(lnk + size_t(NS) * 9); // [NS]
-  int* sinfo = reinterpret_cast<int*>(scoef + NS);                // [NS][5]: ib, x, y, jy, iby
-  const int j = blockIdx.x, dir = blockIdx.y;
-  const int mu = dir & 3;
-  const bool fwd = dir < 4;
-  const double sg = fwd ? -1.0 : 1.0;
+  double* scoef = reinterpret_cast<double*>(lnk + size_t(NS) * 9); // [2][NS]
+  int* sinfo = reinterpret_cast<int*>(scoef + 2 * NS);             // [2][NS][4]: ib, x, jy, iby
+  constexpr int kPx = 6;  // 12 k NS / 256 with 2 k NS <= 256
+  const int j = blockIdx.x, mu = blockIdx.y, dir = mu;
   const int tid = threadIdx.x;
-  const int nrk = (k + TS - 1) / TS;        // row tiles per chirality
-  const int nct = (m + TS - 1) / TS;        // column tiles
-  const bool active = tid < 2 * nrk * nct;
-  const int rt = tid / nct, ct = tid - (tid / nct) * nct;
-  const int al = rt / nrk, i0 = (rt - al * nrk) * TS, c0 = ct * TS;
+  // wavefront: chirality al of the rows, half of the columns; lane: row or column li, step kk
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), al = wv >> 1, u0 = (wv & 1) * RT;
+  const int li = tid & 15, kk = (tid >> 4) & 3;
   const int nface = nd / a.b[mu];
   const int* list = lists + size_t(dir) * nd;  // intra sites, then face sites
   const int nent = m * m;
-  cplx<double> acc[TS][TS];
+  using M = Mm<double>;
+  M::V4 acc[RT][RT];
 
+#pragma unroll 1
   for (int cls = 0; cls < 3; ++cls) {
     // cls 0: intra hops, cls 1: diagonal term (dir 0 only), cls 2: face hops
     if (cls == 1 && dir != 0) continue;
     const int count = cls == 0 ? nd - nface : (cls == 1 ? nd : nface);
     const int base = cls == 2 ? nd - nface : 0;
 #pragma unroll
-    for (int t = 0; t < TS; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int u = 0; u < TS; ++u) acc[t][u] = {0, 0};
-    for (int n0 = 0; n0 < count; n0 += NS) {
-      const int ns = min(NS, count - n0);
-      if (tid < ns) {
-        const int ib = cls == 1 ? n0 + tid : list[base + n0 + tid];
-        const int x = bsite[size_t(j) * nd + ib];
-        int c[4];
-        int rem = x;
-        for (int q = 0; q < 4; ++q) { c[q] = rem % a.L[q]; rem /= a.L[q]; }
-        int cy[4] = {c[0], c[1], c[2], c[3]};
-        if (cls != 1) cy[mu] = fwd ? (c[mu] + 1) % a.L[mu] : (c[mu] + a.L[mu] - 1) % a.L[mu];
-        int cj[4], ci[4];
-        for (int q = 0; q < 4; ++q) { cj[q] = cy[q] / a.b[q]; ci[q] = cy[q] % a.b[q]; }
-        int* si = sinfo + tid * 5;
-        si[0] = ib;
-        si[1] = x;
-        si[2] = lex4(cy, a.L);
-        si[3] = lex4(cj, a.cL);
-        si[4] = lex4(ci, a.b);
-        double sgnbc = 1.0;
-        if (mu == 3 && a.bc_t < 0) {
-          if (fwd && c[3] == a.L[3] - 1) sgnbc = -1.0;
-          if (!fwd && c[3] == 0) sgnbc = -1.0;
+      for (int u = 0; u < RT; ++u) acc[t][u] = M::V4{0.0, 0.0, 0.0, 0.0};
+    // geometry of the sites n0 .. of the class, by the first threads
+    auto stage_info = [&](int n0, int ns, int* info, double* coef) {
+      if (tid >= ns) return;
+      const int ib = cls == 1 ? n0 + tid : list[base + n0 + tid];
+      const int x = bsite[size_t(j) * nd + ib];
+      int c[4];
+      int rem = x;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { c[q] = rem % a.L[q]; rem /= a.L[q]; }
+      int cy[4], cj[4], ci[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cy[q] = cls == 1 || q != mu ? c[q] : (c[q] + 1 == a.L[q] ? 0 : c[q] + 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { cj[q] = cy[q] / a.b[q]; ci[q] = cy[q] % a.b[q]; }
+      int* si = info + tid * 4;
+      si[0] = ib;
+      si[1] = x;
+      si[2] = lex4(cj, a.cL);
+      si[3] = lex4(ci, a.b);
+      coef[tid] = -0.5 * a.cw[mu] * (mu == 3 && a.bc_t < 0 && c[3] == a.L[3] - 1 ? -1.0 : 1.0);
+    };
+    // what a thread stages of them: up to kPx rows of P at the site, a number of a link, and its column of
+    // P at the neighbour
+    typedef double D16 __attribute__((ext_vector_type(16)));  // an array here would go to scratch memory
+    D16 px;
+    cplx<double> qv[6], ln{0, 0};
+    auto load = [&](int ns, const int* info) {
+      ln = {0, 0};  // nothing is kept of the sites before: the registers are free between store and load
+      px = D16(0.0);
+#pragma unroll
+      for (int s6 = 0; s6 < 6; ++s6) qv[s6] = {0, 0};
+      if (tid < ns * 9) {
+        const int q = tid / 9;
+        const double2 v = U[(size_t(mu) * 9 + tid - q * 9) * V + info[q * 4 + 1]];
+        ln = {v.x, v.y};
+      }
+#pragma unroll
+      for (int u = 0; u < kPx; ++u) {
+        const int t = tid + 256 * u;
+        if (t < ns * 12 * k) {
+          const int q = t % ns, rem = t / ns, comp = rem / k, i = rem - comp * k, alc = comp / 6;
+          const double2 v = P[((size_t(j) * 2 + alc) * k + i) * N + size_t(comp - alc * 6) * nd + info[q * 4]];
+          px[2 * u] = v.x;
+          px[2 * u + 1] = v.y;
         }
-        scoef[tid] = -0.5 * a.cw[mu] * sgnbc;
       }
-      __syncthreads();
-      // links and the rows of P at the staged sites
-      for (int t = tid; t < ns * 9; t += 256) {
-        const int q = t / 9, e = t - q * 9;
-        const int* si = sinfo + q * 5;
-        if (fwd) {
-          const double2 v = U[(size_t(mu) * 9 + e) * V + si[1]];
-          lnk[q * 9 + e] = {v.x, v.y};
-        } else {
-          const int rr = e / 3, cc = e - rr * 3;
-          const double2 v = U[(size_t(mu) * 9 + cc * 3 + rr) * V + si[2]];
-          lnk[q * 9 + e] = {v.x, -v.y};
+      if (cls != 1 && tid < ns * m) {
+        const int q = tid / m, col = tid - q * m, beta = col / k;
+        const double2* p = P + ((size_t(info[q * 4 + 2]) * 2 + beta) * k + col - beta * k) * N + info[q * 4 + 3];
+#pragma unroll
+        for (int s6 = 0; s6 < 6; ++s6) {
+          const double2 v = p[size_t(s6) * nd];
+          qv[s6] = {v.x, v.y};
         }
       }
-      for (int t = tid; t < ns * 12 * k; t += 256) {
-        const int q = t % ns, rem = t / ns;
-        const int comp = rem / k, i = rem - comp * k;
-        const int alc = comp / 6, s6 = comp - alc * 6;
-        const double2 v = P[((size_t(j) * 2 + alc) * k + i) * N + size_t(s6) * nd + sinfo[q * 5]];
-        Px[(size_t(q) * 12 + comp) * k + i] = {v.x, v.y};
+    };
+    stage_info(0, min(NS, count), sinfo, scoef);
+    __syncthreads();
+    load(min(NS, count), sinfo);
+#pragma unroll 1
+    for (int n0 = 0, ph = 0; n0 < count; n0 += NS, ph ^= 1) {
+      const int ns = min(NS, count - n0), nx = min(NS, count - n0 - NS);
+      const int* info = sinfo + ph * 4 * NS;
+      const double* coef = scoef + ph * NS;
+      if (tid < ns * 9) lnk[tid] = ln;
+#pragma unroll
+      for (int u = 0; u < kPx; ++u) {
+        const int t = tid + 256 * u;
+        if (t < ns * 12 * k) {
+          const int q = t % ns, rem = t / ns, comp = rem / k;
+          Px[(size_t(q) * 12 + comp) * k + rem - comp * k] = {px[2 * u], px[2 * u + 1]};
+        }
       }
+      stage_info(n0 + NS, nx, sinfo + (ph ^ 1) * 4 * NS, scoef + (ph ^ 1) * NS);
       __syncthreads();
       // H P at the neighbour (cls 1: the diagonal term times P at the site itself)
-      for (int t = tid; t < ns * m; t += 256) {
-        const int q = t / m, col = t - q * m;
+      if (tid < ns * m) {
+        const int q = tid / m, col = tid - q * m;
         const int beta = col / k, l = col - beta * k;
         cplx<double>* hp = HP + size_t(q) * 12 * m + col;
         if (cls == 1 && a.clov) {
           // the chirality-beta block of the site term at the staged site times P's column
-          const double2* blk = a.clov + size_t(beta) * 18 * V + sinfo[q * 5 + 1];
+          const double2* blk = a.clov + size_t(beta) * 18 * V + info[q * 4 + 1];
           cplx<double> x[6];
           for (int s6 = 0; s6 < 6; ++s6) x[s6] = Px[(size_t(q) * 12 + 6 * beta + s6) * k + l];
           cplx<double> y[6];
@@ -410,69 +446,72 @@ __global__ __launch_bounds__(256) void k_build_coarse(const double2* __restrict_
             y[2 * e + 1] = dd.y * x[2 * e + 1];
           }
           int e = 3;
-          for (int i = 0; i < 6; ++i)
+#pragma unroll
+          for (int i = 0; i < 6; ++i) {
+            __builtin_amdgcn_sched_barrier(0);  // a row at a time
+#pragma unroll
             for (int j = i + 1; j < 6; ++j, ++e) {
               const double2 ov = blk[size_t(e) * V];
               const cplx<double> o = {ov.x, ov.y};
               y[i] += o * x[j];
               y[j] += cmul_conj(o, x[i]);
             }
+          }
           for (int comp = 0; comp < 12; ++comp)
             hp[comp * m] = (comp / 6 == beta) ? y[comp - 6 * beta] : cplx<double>{0, 0};
         } else if (cls == 1) {
           for (int comp = 0; comp < 12; ++comp)
             hp[comp * m] = (comp / 6 == beta) ? a.diag * Px[(size_t(q) * 12 + comp) * k + l] : cplx<double>{0, 0};
         } else {
-          const int* si = sinfo + q * 5;
-          cplx<double> qv[6];
-          for (int s6 = 0; s6 < 6; ++s6) {
-            const double2 v = P[((size_t(si[3]) * 2 + beta) * k + l) * N + size_t(s6) * nd + si[4]];
-            qv[s6] = {v.x, v.y};
-          }
-          cplx<double> out[12];
           switch (mu) {
-            case 0: hop_col<0>(qv, beta, sg, lnk + q * 9, scoef[q], out); break;
-            case 1: hop_col<1>(qv, beta, sg, lnk + q * 9, scoef[q], out); break;
-            case 2: hop_col<2>(qv, beta, sg, lnk + q * 9, scoef[q], out); break;
-            default: hop_col<3>(qv, beta, sg, lnk + q * 9, scoef[q], out); break;
-          }
-          for (int comp = 0; comp < 12; ++comp) hp[comp * m] = out[comp];
-        }
-      }
-      __syncthreads();
-      if (active) {
-        for (int q = 0; q < ns; ++q) {
-#pragma unroll 2
-          for (int s6 = 0; s6 < 6; ++s6) {
-            const int comp = 6 * al + s6;
-            const cplx<double>* pr = Px + (size_t(q) * 12 + comp) * k;
-            const cplx<double>* hr = HP + (size_t(q) * 12 + comp) * m;
-            cplx<double> pa[TS], hb[TS];
-#pragma unroll
-            for (int t = 0; t < TS; ++t) pa[t] = (i0 + t < k) ? pr[i0 + t] : cplx<double>{0, 0};
-#pragma unroll
-            for (int u = 0; u < TS; ++u) hb[u] = (c0 + u < m) ? hr[c0 + u] : cplx<double>{0, 0};
-#pragma unroll
-            for (int t = 0; t < TS; ++t)
-#pragma unroll
-              for (int u = 0; u < TS; ++u) acc[t][u] += cmul_conj(pa[t], hb[u]);
+            case 0: hop_col<0>(qv, beta, -1.0, lnk + q * 9, coef[q], hp, m); break;
+            case 1: hop_col<1>(qv, beta, -1.0, lnk + q * 9, coef[q], hp, m); break;
+            case 2: hop_col<2>(qv, beta, -1.0, lnk + q * 9, coef[q], hp, m); break;
+            default: hop_col<3>(qv, beta, -1.0, lnk + q * 9, coef[q], hp, m); break;
           }
         }
       }
       __syncthreads();
-    }
-    // write: intra hops to W[dir], the diagonal term to W[4], face hops to Y_{1+dir}
-    if (active) {
-      for (int t = 0; t < TS; ++t)
-        for (int u = 0; u < TS; ++u) {
-          const int i = i0 + t, col = c0 + u;
-          if (i >= k || col >= m) continue;
-          const int idx = col * m + al * k + i;
-          const double2 v = make_double2(acc[t][u].re, acc[t][u].im);
-          if (cls == 2) Y[(size_t(j) * 9 + 1 + dir) * nent + idx] = v;
-          else W[(size_t(cls == 1 ? 4 : dir) * a.d + j) * nent + idx] = v;
+      if (nx > 0) load(nx, sinfo + (ph ^ 1) * 4 * NS);  // in flight during the products
+      const double* pd = reinterpret_cast<const double*>(Px);
+      const double* hd = reinterpret_cast<const double*>(HP);
+#pragma unroll 1
+      for (int s4 = 0; s4 < 6 * ns; s4 += 4) {
+        const int kc = min(s4 + kk, 6 * ns - 1), q = kc / 6, row = q * 6 + 6 * al + kc;  // 12 q + 6 al + kc % 6
+        const bool in = s4 + kk < 6 * ns;
+        double pa[RT], hb[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          const double v = pd[size_t(row) * 2 * k + min(16 * t + li, 2 * k - 1)];
+          pa[t] = in ? v : 0.0;
         }
+#pragma unroll
+        for (int u = 0; u < RT; ++u) {
+          const double v = hd[size_t(row) * 2 * m + min(16 * (u0 + u) + li, 2 * m - 1)];
+          hb[u] = in ? v : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+          for (int u = 0; u < RT; ++u) acc[t][u] = M::mul(pa[t], hb[u], acc[t][u]);
+      }
+      __syncthreads();
     }
+    // write: intra hops to W[dir], the diagonal term to W[4], face hops to Y_{1+dir}.  Rows 2i, 2i + 1 and
+    // columns 2c, 2c + 1 meet in lanes that differ in 17: Re = rr + ii, Im = ri - ir.
+    double* dst = reinterpret_cast<double*>(cls == 2 ? Y + (size_t(j) * 9 + 1 + dir) * nent
+                                                     : W + (size_t(cls == 1 ? 4 : dir) * a.d + j) * nent);
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int u = 0; u < RT; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double own = acc[t][u][v], x = __shfl_xor(own, 17);
+          const int r2 = 16 * t + M::row(tid & 63, v), c2 = 16 * (u0 + u) + li;
+          if ((kk & 1) == 0 && r2 < 2 * k && c2 < 2 * m)
+            dst[(size_t(c2 >> 1) * m + al * k + (r2 >> 1)) * 2 + (c2 & 1)] = (li & 1) ? own - x : own + x;
+        }
   }
 }
 
@@ -1050,12 +1089,13 @@ void build_coarse(HierarchyDev& h, hipStream_t st) {
                  double(h.g.V) * 4.0 * (2.0 * h.k) * (2.0 * h.k) * 6.0 * 8.0, false);
   const int nent = 4 * h.k * h.k;
   DevBuf W(size_t(8) * h.blk.d * nent * sizeof(double2));
-  // per site: Px (12 k) + HP (24 k) + link (9) complex, + coefficient and 5 ints
-  const size_t per_site = size_t(12 * h.k + 24 * h.k + 9) * sizeof(cplx<double>) + sizeof(double) + 5 * sizeof(int);
+  // per site: Px (12 k) + HP (24 k) + link (9) complex, + coefficient and 4 ints of two phases
+  const size_t per_site =
+      size_t(12 * h.k + 24 * h.k + 9) * sizeof(cplx<double>) + 2 * (sizeof(double) + 4 * sizeof(int));
   // sites staged per phase within 76 KB of LDS, so that two workgroups share a CU (their
-  // register use allows two) and one's loads overlap the other's products: at 32^3 x 64, k = 24
-  // (5 sites) 70 ms against 106 ms with 110 KB (one workgroup per CU); smaller budgets are slower
-  const int NS = int(std::max<size_t>(1, std::min<size_t>(16, (76 * 1024) / per_site)));
+  // register use allows two) and one's hops overlap the other's products; a thread takes at most one
+  // column of H P and kPx numbers of P
+  const int NS = int(std::max<size_t>(1, std::min<size_t>({16, (76 * 1024) / per_site, size_t(128 / h.k)})));
   const size_t lds = per_site * NS;
   auto go = [&](auto kern) {
     if (lds > 64 * 1024) QMG_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1063,7 +1103,9 @@ void build_coarse(HierarchyDev& h, hipStream_t st) {
     kern<<<dim3(h.blk.d, 4), 256, lds, st>>>(h.U64.as<double2>(), h.P64.as<double2>(), h.bsite.as<int>(),
                                              h.blists.as<int>(), h.Y64.as<double2>(), W.as<double2>(), a, NS);
   };
-  if (h.k <= 24) go(k_build_coarse<3>);
+  if (h.k <= 8) go(k_build_coarse<1>);
+  else if (h.k <= 16) go(k_build_coarse<2>);
+  else if (h.k <= 24) go(k_build_coarse<3>);
   else go(k_build_coarse<4>);
   QMG_LAUNCH_CHECK();
   k_sum_self<<<cdiv(size_t(h.blk.d) * nent, 256), 256, 0, st>>>(W.as<double2>(), h.Y64.as<double2>(), h.blk.d,

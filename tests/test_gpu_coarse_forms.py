@@ -39,3 +39,23 @@ def test_coarse_forms(qmg, dims, rank, prec):
         assert rel(to_np(qmg.coarse_apply(mg, v[:nrhs])), ref[:nrhs]) < TOL[prec], nrhs
         assert rel(to_np(qmg.coarse_schur_apply(mg, half[:nrhs])), to_np(one[:nrhs])) < 2 * TOL[prec], nrhs
     mg.close()
+
+
+# ranks at the edges of the tiles; blocks of 16, 36, 8 and 12 sites (whole, ragged and single-site stages,
+# an extent without hops inside the block)
+BUILD = [((4, 4, 4, 4), (2, 2, 2, 2), 1), ((4, 4, 4, 4), (2, 2, 2, 2), 8), ((4, 4, 4, 4), (2, 2, 2, 2), 9),
+         ((6, 6, 4, 4), (3, 3, 2, 2), 16), ((6, 6, 4, 4), (3, 3, 2, 2), 17), ((4, 4, 4, 2), (2, 2, 2, 1), 24),
+         ((6, 4, 4, 4), (3, 2, 2, 1), 25), ((4, 4, 4, 8), (2, 2, 2, 4), 32)]
+
+
+@pytest.mark.parametrize("dims,block,rank", BUILD)
+def test_coarse_build_forms(qmg, dims, block, rank):
+    banner(f"coarse build {dims} block {block} rank {rank}")
+    m, xi = -0.1, 2.0
+    U = fields.random_gauge(dims, 0.4, 33)
+    lat = qmg.Lattice(dims, m, xi, -1)
+    mg = qmg.mg_setup_stream_chiral_svd(lat, to_gpu(U), block, rank, rank, rank, n_setup_iter=0, inner="f64", seed=5)
+    ref = coarse.build_coarse(U, to_np(mg.prolongator()[0]), m, xi, -1, dims, block)
+    # sums of at most 6 * 36 products and ten terms each: below 250 roundings, half of them of either side
+    assert rel(to_np(mg.coarse_blocks()), ref) < 3e-14
+    mg.close()
