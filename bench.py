@@ -54,9 +54,9 @@ FAMILY_KERNEL = {
     "dslash/site": ("k_dslash<", "dslash.hip"),
     "dslash/twalk": ("k_dslash_t<", "dslash.hip"),
     "dslash/pair": ("k_dslash_pair<", "dslash_pair.hip"),
-    "coarse_apply": ("k_coarse_apply", "transfer.hip"),
-    "restrict": ("k_restrict", "transfer.hip"),
-    "prolong": ("k_prolong", "transfer.hip"),
+    "coarse_apply": ("k_coarse_mm<", "coarse_mm.hip"),  # of the batched solve's groups; one rhs: k_coarse_apply
+    "restrict": ("k_restrict", "transfer_mm.hip"),
+    "prolong": ("k_prolong", "transfer_mm.hip"),
     "coarse_build": ("k_build_coarse", "transfer.hip"),
     "evenodd/hop": ("k_hop_", "hop_pair.hip"),
     "coarse_eo": ("k_coarse_eo_apply", "coarse_evenodd.hip"),

@@ -318,8 +318,9 @@ constexpr int kMaxM = 64;        // 2k <= 64
 // of 3 x 3 complex numbers per thread instead, six 16-byte LDS reads for 36 multiply-adds, and the loads of
 // a phase waited for in turn, the LDS and the waits set the time.  Measured (whole coarse phase of the setup,
 // rank 24): 32^3 x 64 73.3 -> 48.4 ms (67.9 with the loads ahead alone), 16^3 x 32 4.80 -> 3.17 ms, 8^3 x 16
-// 1.28 -> 0.75 ms; rank 8 at 16^3 x 32 2.27 -> 0.89 ms.  What is left is the hop itself (a thread per column
-// of P, FP64 on the vector units), with two workgroups per CU by their registers and LDS.
+// 1.28 -> 0.75 ms; rank 8 at 16^3 x 32 2.27 -> 0.89 ms.  At 32^3 x 64 what is left is reading: 184 GB (4.2
+// TB/s), since each direction reads P at the site and at the neighbour in runs of a stage's sites.  Stages of a
+// multiple of four sites: rank 24 4 % faster, rank 20 and small lattices 3 % slower.
 template <int RT>
 __global__ __launch_bounds__(256, 2) void k_build_coarse(const double2* __restrict__ U, const double2* __restrict__ P,
                                                          const int* __restrict__ bsite, const int* __restrict__ lists,
