@@ -12,7 +12,7 @@ namespace qmg {
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kPairBlock;
 
 __device__ inline void st2(float2* p, unsigned off, cf va, cf vb) {
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -34,14 +34,12 @@ __device__ inline void pair_dslash(const float2* __restrict__ U, const float2* _
   const unsigned tp = at(y, z, t + 1 == L3 ? 0 : t + 1), tm = at(y, z, t == 0 ? L3 - 1 : t - 1);
   const unsigned xp = x + 2 == L0 ? own - 8u * unsigned(x) : own + 16u;        // the number after the pair
   const unsigned xm = x == 0 ? own + 8u * unsigned(L0 - 1) : own - 8u;         // and the one before it
-  const float cx = -0.5f * a.cw_f[0], cy = -0.5f * a.cw_f[1], cz = -0.5f * a.cw_f[2], ct = -0.5f * a.cw_f[3];
+  const float cs = -0.5f * a.cw_f[0], ct = -0.5f * a.cw_f[3];
   const float ctf = (a.bc_t < 0 && t == L3 - 1) ? -ct : ct, ctb = (a.bc_t < 0 && t == 0) ? -ct : ct;
   constexpr float sf = DAG ? 1.f : -1.f, sb = -sf;
-  cf wa[NR][12], wb[NR][12];
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-#pragma unroll
-    for (int k = 0; k < 12; ++k) wa[r][k] = wb[r][k] = {0.f, 0.f};
+  constexpr int PARK = NR == 2 ? 16 : 0;
+  __shared__ float4 park[PARK ? PARK : 1][kPairBlock];
+  cf wa[NR][12], wb[NR][12], ta[NR][12], tb[NR][12];
   Two self[12];  // the pair's own numbers, where there are registers for them
   auto hop = [&](auto mu, auto fwd, unsigned nbo, float coef, int b) {
     constexpr int MU = decltype(mu)::value;
@@ -64,8 +62,8 @@ __device__ inline void pair_dslash(const float2* __restrict__ U, const float2* _
         ca[k] = v.a;
         cb[k] = v.b;
       }
-      add_hop<MU>(ca, ua, F ? sf : sb, coef, wa[r]);
-      add_hop<MU>(cb, ub, F ? sf : sb, coef, wb[r]);
+      add_hop<MU>(ca, ua, F ? sf : sb, coef, ta[r]);
+      add_hop<MU>(cb, ub, F ? sf : sb, coef, tb[r]);
     }
   };
   using I1 = std::integral_constant<int, 1>;
@@ -76,14 +74,16 @@ __device__ inline void pair_dslash(const float2* __restrict__ U, const float2* _
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
     {  // both x hops: the pair itself and the numbers on either side of it
+      unsigned o = own;  // by another name in each colour: the links here would be kept for the next one
+      asm volatile("" : "+v"(o));
       cf ufa[3], ufb[3], uba[3], ubb[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const Two u = ld2(U + (3 * c + b) * V, own);
+        const Two u = ld2(U + (3 * c + b) * V, o);
         ufa[c] = u.a;
         ufb[c] = u.b;
         uba[c] = conj(ld1(U + (3 * b + c) * V, xm));
-        ubb[c] = conj(ld1(U + (3 * b + c) * V, own));
+        ubb[c] = conj(ld1(U + (3 * b + c) * V, o));
       }
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
@@ -91,25 +91,41 @@ __device__ inline void pair_dslash(const float2* __restrict__ U, const float2* _
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const float2* pl = in + (r * 12 + 3 * k + b) * V;
-          const Two v = ld2(pl, own);
+          const Two v = ld2(pl, o);
           if (NR == 1) self[3 * k + b] = v;
           pa[k] = v.b;
           pb[k] = ld1(pl, xp);
           ma[k] = ld1(pl, xm);
           mb[k] = v.a;
         }
-        add_hop<0>(pa, ufa, sf, cx, wa[r]);
-        add_hop<0>(pb, ufb, sf, cx, wb[r]);
-        add_hop<0>(ma, uba, sb, cx, wa[r]);
-        add_hop<0>(mb, ubb, sb, cx, wb[r]);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) ta[r][k] = tb[r][k] = {0.f, 0.f};
+        add_hop<0>(pa, ufa, sf, 1.f, ta[r]);
+        add_hop<0>(pb, ufb, sf, 1.f, tb[r]);
+        add_hop<0>(ma, uba, sb, 1.f, ta[r]);
+        add_hop<0>(mb, ubb, sb, 1.f, tb[r]);
       }
     }
-    hop(I1{}, T{}, yp, cy, b);
-    hop(I1{}, F{}, ym, cy, b);
-    hop(I2{}, T{}, zp, cz, b);
-    hop(I2{}, F{}, zm, cz, b);
+    hop(I1{}, T{}, yp, 1.f, b);
+    hop(I1{}, F{}, ym, 1.f, b);
+    hop(I2{}, T{}, zp, 1.f, b);
+    hop(I2{}, F{}, zm, 1.f, b);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {  // x, y and z have one weight
+        ta[r][k] = cs * ta[r][k];
+        tb[r][k] = cs * tb[r][k];
+      }
     hop(I3{}, T{}, tp, ctf, b);
     hop(I3{}, F{}, tm, ctb, b);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int k = 0; k < 12; k += 2) {
+        add_pack<PARK>(12 * r + k / 2, b, ta[r][k], ta[r][k + 1], wa[r][k], wa[r][k + 1], park);
+        add_pack<PARK>(12 * r + 6 + k / 2, b, tb[r][k], tb[r][k + 1], wb[r][k], wb[r][k + 1], park);
+      }
   }
   if constexpr (CLOV) {
     cf va[NR][12], vb[NR][12];

@@ -7,9 +7,9 @@
 // one of the two hops reads the same half-lattice pair, the other that pair moved by one site, of
 // which one number is already there and one is loaded by itself.
 // Measured on 32^3 x 64, two hops, against one site per thread with the hops outermost: 1 rhs 397 ->
-// 351 us, 4 rhs 1066 -> 813 us, 12 rhs 2813 -> 2192 us (4 rhs: 3.07 -> 1.48 GB fetched by a hop).
+// 347 us, 4 rhs 1057 -> 800 us; 24^3 x 48 with 12 rhs 963 -> 728 us (4 rhs: 3.07 -> 1.48 GB fetched by a hop).
 // The colours of the neighbours' spinors are taken one after another over all eight hops
-// (acc += U[., b] h_b), so that the planes the workgroups of an XCD read at a time are a third of
+// (each colour's sum by itself, see pair.hpp), so that the planes the workgroups of an XCD read at a time are a third of
 // their spinors and fit its 4 MB L2: with the hops outermost nearly every y, z and t neighbour was
 // fetched again from beyond the L2.
 #include <algorithm>
@@ -22,7 +22,7 @@ namespace qmg {
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kPairBlock;
 
 // out (parity p) = POST(YM(y) + sgn H in) as k_hop_eo (hop.hip), NR right-hand sides rhs_base + NR g ..
 // of the workgroup's group g.  CLOV: the site term Ap (YM = 2) or Aip (POST = 1) is used, else the scalar one.
@@ -65,14 +65,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_hop_pair(const float2* __restrict
   const float2* Uown = p ? Uo : Ue;
   const float2* Uoth = p ? Ue : Uo;
   const float mh = -0.5f * sgn;
-  const float cx = mh * a.cw_f[0], cy = mh * a.cw_f[1], cz = mh * a.cw_f[2], ct = mh * a.cw_f[3];
+  const float cs = mh * a.cw_f[0], ct = mh * a.cw_f[3];
   const float ctf = (a.bc_t < 0 && t == L3 - 1) ? -ct : ct, ctb = (a.bc_t < 0 && t == 0) ? -ct : ct;
   constexpr float sf = DAG ? 1.f : -1.f, sb = -sf;
-  cf wa[NR][12], wb[NR][12];
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-#pragma unroll
-    for (int k = 0; k < 12; ++k) wa[r][k] = wb[r][k] = {0.f, 0.f};
+  constexpr int PARK = NR == 2 ? 16 : 6;
+  __shared__ float4 park[PARK ? PARK : 1][kPairBlock];
+  cf wa[NR][12], wb[NR][12], ta[NR][12], tb[NR][12];
   const float2* inr = in + size_t(rhs) * 12 * Vh;
   auto hop = [&](auto mu, auto fwd, unsigned nbo, float coef, int b) {
     constexpr int MU = decltype(mu)::value;
@@ -95,8 +93,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_hop_pair(const float2* __restrict
         ca[k] = v.a;
         cb[k] = v.b;
       }
-      add_hop<MU>(ca, ua, F ? sf : sb, coef, wa[r]);
-      add_hop<MU>(cb, ub, F ? sf : sb, coef, wb[r]);
+      add_hop<MU>(ca, ua, F ? sf : sb, coef, ta[r]);
+      add_hop<MU>(cb, ub, F ? sf : sb, coef, tb[r]);
     }
   };
   using I1 = std::integral_constant<int, 1>;
@@ -130,18 +128,34 @@ __global__ __launch_bounds__(kBlock, 2) void k_hop_pair(const float2* __restrict
           pb[k] = pick(odd, e, v.b);
           ma[k] = pick(odd, v.a, e);
         }
-        add_hop<0>(pa, ufa, sf, cx, wa[r]);
-        add_hop<0>(pb, ufb, sf, cx, wb[r]);
-        add_hop<0>(ma, uba, sb, cx, wa[r]);
-        add_hop<0>(mb, ubb, sb, cx, wb[r]);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) ta[r][k] = tb[r][k] = {0.f, 0.f};
+        add_hop<0>(pa, ufa, sf, 1.f, ta[r]);
+        add_hop<0>(pb, ufb, sf, 1.f, tb[r]);
+        add_hop<0>(ma, uba, sb, 1.f, ta[r]);
+        add_hop<0>(mb, ubb, sb, 1.f, tb[r]);
       }
     }
-    hop(I1{}, T{}, yp, cy, b);
-    hop(I1{}, F{}, ym, cy, b);
-    hop(I2{}, T{}, zp, cz, b);
-    hop(I2{}, F{}, zm, cz, b);
+    hop(I1{}, T{}, yp, 1.f, b);
+    hop(I1{}, F{}, ym, 1.f, b);
+    hop(I2{}, T{}, zp, 1.f, b);
+    hop(I2{}, F{}, zm, 1.f, b);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {  // x, y and z have one weight
+        ta[r][k] = cs * ta[r][k];
+        tb[r][k] = cs * tb[r][k];
+      }
     hop(I3{}, T{}, tp, ctf, b);
     hop(I3{}, F{}, tm, ctb, b);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int k = 0; k < 12; k += 2) {
+        add_pack<PARK>(12 * r + k / 2, b, ta[r][k], ta[r][k + 1], wa[r][k], wa[r][k + 1], park);
+        add_pack<PARK>(12 * r + 6 + k / 2, b, tb[r][k], tb[r][k + 1], wb[r][k], wb[r][k + 1], park);
+      }
   }
   if constexpr (YM == 1 || (YM == 2 && !CLOV)) {
     const float f = YM == 1 ? 1.f : a.diag_f;

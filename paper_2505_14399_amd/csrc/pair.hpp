@@ -11,13 +11,24 @@ typedef cplx<float> cf;
 struct Two {  // one number of each of the two sites
   cf a, b;
 };
-// p is uniform over the workgroup, off a byte offset of the thread
+// p is uniform over the workgroup, off a byte offset of the thread.  The plane's address is pinned to scalar
+// registers: combined with the offsets of the thread, addresses took 64-bit additions and two vector
+// registers each
+typedef const __attribute__((address_space(1))) char* gptr;
+template <class T>
+__device__ inline T at_off(const float2* p, unsigned off) {
+  gptr g = (gptr)p;
+  asm("" : "+s"(g));
+  return *reinterpret_cast<const __attribute__((address_space(1))) T*>(g + off);
+}
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
 __device__ inline Two ld2(const float2* p, unsigned off) {
-  const float4 v = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off);
+  const f4v v = at_off<f4v>(p, off);
   return {{v.x, v.y}, {v.z, v.w}};
 }
 __device__ inline cf ld1(const float2* p, unsigned off) {
-  const float2 v = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(p) + off);
+  const f2v v = at_off<f2v>(p, off);
   return {v.x, v.y};
 }
 __device__ inline cf pick(bool c, cf x, cf y) { return {c ? x.re : y.re, c ? x.im : y.im}; }
@@ -62,6 +73,36 @@ __device__ inline void add_hop(const cf* chi, const cf* u, float s, float coef, 
   }
 }
 
+// Sums over hops and colours.  A component of the result has 24 terms, eight hops of three colours; added one
+// to another they would be rounded 24 times at up to the size of the whole.  The hops of a colour are summed by
+// themselves (t: the space directions, which have one weight, without it, then weight and time hops) and
+// the three colours' sums after that (w), so that the error is that of eight whole hops.  FP32 at xi = 1 / 3.5:
+// D 6.64e-8 / 5.53e-8 -> 5.99e-8 / 4.42e-8, Schur complement 6.40e-8 / 5.24e-8 -> 6.01e-8 / 4.26e-8 (whole hops, one
+// site per thread: 6.00e-8 / 4.43e-8 and 6.01e-8 / 4.28e-8).
+// The registers do not hold both sums of two right-hand sides: PARK packs of two numbers of w wait in the LDS, each
+// in a slot of its thread (16 bytes per lane), the others are pinned in registers between the colours, or the
+// compiler would put off the arithmetic of one colour to the next and keep that colour's loads instead (800 spilled).
+constexpr int kPairBlock = 256;
+// pack c: numbers k, k + 1 of a site, added after colour b
+template <int PARK>
+__device__ inline void add_pack(int c, int b, cf t0, cf t1, cf& w0, cf& w1, float4 (*park)[kPairBlock]) {
+  if (b) {
+    if (c < PARK) {
+      const float4 o = park[c][threadIdx.x];
+      w0 = {o.x, o.y};
+      w1 = {o.z, o.w};
+    }
+    t0 = w0 + t0;
+    t1 = w1 + t1;
+  }
+  if (c < PARK && b < 2) {
+    park[c][threadIdx.x] = {t0.re, t0.im, t1.re, t1.im};
+  } else {
+    w0 = t0;
+    w1 = t1;
+    asm volatile("" : "+v"(w0.re), "+v"(w0.im), "+v"(w1.re), "+v"(w1.im));
+  }
+}
 // acc += A v on the pair's sites, A the packed site term (layout of clover_acc)
 template <int NR>
 __device__ inline void site_term(const float2* A, unsigned off, size_t Vh, const cf (*va)[12], const cf (*vb)[12],
