@@ -420,6 +420,9 @@ __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, 
   for (int k = 0; k < 12; ++k) part[mu][k][lane] = acc[0][k];
   __syncthreads();
   if (!live) return;
+  auto sum = [&](int k, C d, cplx<C> o) {
+    return sum_directions(part[0][k][lane], part[1][k][lane], part[2][k][lane], part[3][k][lane], d, o);
+  };
   if constexpr (CLOV) {
     // wavefront mu writes rows 3 (mu & 1) .. +2 of chirality mu >> 1 (uniform in the wavefront)
     const int al = mu >> 1;
@@ -432,20 +435,14 @@ __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, 
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int k = 3 * mu + q;
-      cplx<C> v = y[q];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) v += part[m][k][lane];
-      stc(outr, size_t(k) * V + site, v);
+      stc(outr, size_t(k) * V + site, sum(k, C(1), y[q]));
     }
   } else {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int k = 3 * mu + q;
       const size_t i = size_t(k) * V + site;
-      cplx<C> v = diag * ldc(inr, i);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) v += part[m][k][lane];
-      stc(outr, i, v);
+      stc(outr, i, sum(k, diag, ldc(inr, i)));
     }
   }
 }

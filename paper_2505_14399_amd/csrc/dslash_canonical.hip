@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, sizeof(S) == 16 ? 2 : 1) void k_dslash_canon(c
     }
 #pragma unroll
     for (int k = 0; k < 12; ++k) mine[k * kSites + lane] = acc[k];
-    cplx<C> v[3];
+    cplx<C> own3[3];  // of this wavefront's components: the site term's, or the spinor's numbers
     if constexpr (CLOV) {
       // rows 3 (mu & 1) .. +2 of chirality mu >> 1
       const int al = mu >> 1;
@@ -169,17 +169,20 @@ __global__ __launch_bounds__(256, sizeof(S) == 16 ? 2 : 1) void k_dslash_canon(c
 #pragma unroll
       for (int j = 0; j < 6; ++j) xv[j] = StoreTraits<S>::ld(raw<S>(inr + 6 * al + j, own));
       const S* b = static_cast<const S*>(a.clov) + size_t(al) * 18 * V + site;
-      if (mu & 1) site_term_rows<S, 3>(b, V, xv, v);
-      else site_term_rows<S, 0>(b, V, xv, v);
+      if (mu & 1) site_term_rows<S, 3>(b, V, xv, own3);
+      else site_term_rows<S, 0>(b, V, xv, own3);
     } else {
 #pragma unroll
-      for (int q = 0; q < 3; ++q) v[q] = diag * StoreTraits<S>::ld(raw<S>(inr + 3 * mu + q, own));
+      for (int q = 0; q < 3; ++q) own3[q] = StoreTraits<S>::ld(raw<S>(inr + 3 * mu + q, own));
     }
     __syncthreads();
+    cplx<C> v[3];
+    auto part = [&](int m, int k) { return reinterpret_cast<const cplx<C>*>(smem[m])[k * kSites + lane]; };
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) v[q] += reinterpret_cast<const cplx<C>*>(smem[m])[(3 * mu + q) * kSites + lane];
+    for (int q = 0; q < 3; ++q) {
+      const int k = 3 * mu + q;
+      v[q] = sum_directions(part(0, k), part(1, k), part(2, k), part(3, k), CLOV ? C(1) : diag, own3[q]);
+    }
     __syncthreads();
     if (live) {
 #pragma unroll
