@@ -239,6 +239,7 @@ void launch_dslash_pair(const void* U, const void* in, void* out, const DslashAr
   using F = std::false_type;
   if (a.clov) a.dagger ? run(T{}, T{}) : run(F{}, T{});
   else a.dagger ? run(T{}, F{}) : run(F{}, F{});
+  QMG_LAUNCH_CHECK();
 }
 
 void launch_dslash_pair_padded(const BatchLattice* lat, int nl, int nr, int Vpad, const void* U, const void* in,
@@ -256,6 +257,7 @@ void launch_dslash_pair_padded(const BatchLattice* lat, int nl, int nr, int Vpad
   };
   if (nr % 2 == 0) run(std::integral_constant<int, 2>{});
   else run(std::integral_constant<int, 1>{});
+  QMG_LAUNCH_CHECK();
 }
 
 }  // namespace qmg
