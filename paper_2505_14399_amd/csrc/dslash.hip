@@ -418,32 +418,30 @@ __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, 
   }
 #pragma unroll
   for (int k = 0; k < 12; ++k) part[mu][k][lane] = acc[0][k];
+  cplx<C> own[3];  // of components 3 mu .. : the spinor's numbers, or the site term's
+  if (live) {
+    if constexpr (CLOV) {
+      // rows 3 (mu & 1) .. +2 of chirality mu >> 1 (uniform in the wavefront)
+      const int al = mu >> 1;
+      cplx<C> x[6];
+#pragma unroll
+      for (int j = 0; j < 6; ++j) x[j] = ldc(inr, size_t(6 * al + j) * V + site);
+      const S* b = static_cast<const S*>(a.clov) + size_t(al) * 18 * V + site;
+      if (mu & 1) site_term_rows<S, 3>(b, V, x, own);
+      else site_term_rows<S, 0>(b, V, x, own);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) own[q] = ldc(inr, size_t(3 * mu + q) * V + site);
+    }
+  }
   __syncthreads();
   if (!live) return;
-  auto sum = [&](int k, C d, cplx<C> o) {
-    return sum_directions(part[0][k][lane], part[1][k][lane], part[2][k][lane], part[3][k][lane], d, o);
-  };
-  if constexpr (CLOV) {
-    // wavefront mu writes rows 3 (mu & 1) .. +2 of chirality mu >> 1 (uniform in the wavefront)
-    const int al = mu >> 1;
-    cplx<C> x[6], y[3];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) x[j] = ldc(inr, size_t(6 * al + j) * V + site);
-    const S* b = static_cast<const S*>(a.clov) + size_t(al) * 18 * V + site;
-    if (mu & 1) site_term_rows<S, 3>(b, V, x, y);
-    else site_term_rows<S, 0>(b, V, x, y);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int k = 3 * mu + q;
-      stc(outr, size_t(k) * V + site, sum(k, C(1), y[q]));
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int k = 3 * mu + q;
-      const size_t i = size_t(k) * V + site;
-      stc(outr, i, sum(k, diag, ldc(inr, i)));
-    }
+  for (int q = 0; q < 3; ++q) {
+    const int k = 3 * mu + q;
+    stc(outr, size_t(k) * V + site,
+        sum_directions<S>(part[0][k][lane], part[1][k][lane], part[2][k][lane], part[3][k][lane], CLOV ? C(1) : diag,
+                          own[q]));
   }
 }
 

@@ -181,7 +181,12 @@ __global__ __launch_bounds__(256, sizeof(S) == 16 ? 2 : 1) void k_dslash_canon(c
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int k = 3 * mu + q;
-      v[q] = sum_directions(part(0, k), part(1, k), part(2, k), part(3, k), CLOV ? C(1) : diag, own3[q]);
+      const cplx<C> p0 = part(0, k), p1 = part(1, k), p2 = part(2, k), p3 = part(3, k);
+      if constexpr (sizeof(C) == 8 && !CLOV)
+        v[q] = {sum_compensated(p0.re, p1.re, p2.re, p3.re, diag, own3[q].re),
+                sum_compensated(p0.im, p1.im, p2.im, p3.im, diag, own3[q].im)};
+      else
+        v[q] = sum_directions<S>(p0, p1, p2, p3, CLOV ? C(1) : diag, own3[q]);
     }
     __syncthreads();
     if (live) {

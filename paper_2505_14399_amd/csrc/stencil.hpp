@@ -87,28 +87,38 @@ __device__ inline void su3_mul(const cplx<C>* u, const cplx<C>* h, cplx<C>* w) {
   }
 }
 
-// p0 + p1 + p2 + p3 + d o, each addition with its rounding error, which are added up and in at the end, so that
-// the direction-split stencils, whose four partial sums meet here, are rounded once where they do.
-// (Plain additions with the large diagonal term first were rounded five times at its size; relative
-// error in FP32 at xi = 1 / 3.5: 7.1e-8 / 5.8e-8, plain with that term last 5.9e-8 / 4.5e-8, and 5.6e-8 / 4.2e-8 here.)
-template <class C>
-__device__ inline C sum_directions(C p0, C p1, C p2, C p3, C d, C o) {
-  C s = p0, e = 0;
-  auto add = [&](C x) {
-    const C t = s + x, b = t - s;
+// p0 + p1 + p2 + p3 + d o: the four partial sums of the direction-split stencils and the large diagonal term, which
+// comes last (added first, every sum is rounded at its size).  In FP32 in double, rounded once: relative error
+// at xi = 1 / 3.5 5.6e-8 / 4.2e-8, plain 5.9e-8 / 4.5e-8, diagonal first 7.1e-8 / 5.8e-8.  16-bit storage rounds the result
+// ten thousand times coarser, and the site term of the clover form (d = 1) has roundings of its own.
+template <class S>
+__device__ inline cplx<ctype<S>> sum_directions(cplx<ctype<S>> p0, cplx<ctype<S>> p1, cplx<ctype<S>> p2,
+                                                cplx<ctype<S>> p3, ctype<S> d, cplx<ctype<S>> o) {
+  if constexpr (StoreTraits<S>::prec == QMG_F32) {
+    auto sum = [&](float a, float b, float c, float e, float f) {
+      return float(fma(double(d), double(f), ((double(a) + double(b)) + double(c)) + double(e)));
+    };
+    return {sum(p0.re, p1.re, p2.re, p3.re, o.re), sum(p0.im, p1.im, p2.im, p3.im, o.im)};
+  } else {
+    return ((p0 + p1) + p2) + p3 + d * o;
+  }
+}
+// the same with each addition's rounding error, which are summed and added at the end (FP64 canonical 1.14e-16 /
+// 1.18e-16, plain 1.17e-16 / 1.19e-16, diagonal first 1.39e-16 / 1.37e-16; eight hops and the diagonal term one by one
+// 1.16e-16 / 1.17e-16)
+__device__ inline double sum_compensated(double p0, double p1, double p2, double p3, double d, double o) {
+  double s = p0, e = 0;
+  auto add = [&](double x) {
+    const double t = s + x, b = t - s;
     e += (s - (t - b)) + (x - b);
     s = t;
   };
   add(p1);
   add(p2);
   add(p3);
-  const C t = fma(d, o, s), b = t - s;
+  const double t = fma(d, o, s), b = t - s;
   e += (s - (t - b)) + fma(d, o, -b);
   return t + e;
-}
-template <class C>
-__device__ inline cplx<C> sum_directions(cplx<C> p0, cplx<C> p1, cplx<C> p2, cplx<C> p3, C d, cplx<C> o) {
-  return {sum_directions(p0.re, p1.re, p2.re, p3.re, d, o.re), sum_directions(p0.im, p1.im, p2.im, p3.im, d, o.im)};
 }
 
 // NE = 6: native links stored as their first two rows ([mu][6][V]); the third row of an SU(3)
