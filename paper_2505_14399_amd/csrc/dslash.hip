@@ -634,7 +634,13 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
   // 32^3 x 64 with 4 rhs 1186 / 937, 12 rhs 2994 / 2704, 1 rhs 413 / 420).  Below 2^17 sites x rhs half
   // the threads are too few (18 x 5 x 9 x 13, 3 rhs: 9.0 / 10.0).
   const long work = long(a.V) * a.nrhs;
-  if (pairs && work >= (1L << 17) && (work < (1L << 21) || (clov && a.nrhs > 1)))
+  // One right-hand side, against the direction split, whose workgroups are small: a last round of 512 sites to
+  // each of the 256 CUs that is not nearly full costs more than the loads save (rounds, us, direction split /
+  // pairs: 16^3 x 36 1.1, 17.0 / 19.9; 18^3 x 32 1.4, 22.3 / 23.7; 20^3 x 28 1.7, 26.0 / 25.0; 16^2 x 32^2 2.0, 31.0 / 27.8;
+  // 20^3 x 40 2.4, 35.5 / 37.5), from the fourth round on no longer (24^3 x 32 3.4, 48.7 / 47.6).
+  const long ntile = (long(a.V) + 511) / 512, rounds = (ntile + 255) / 256;
+  const bool full = a.nrhs > 1 || rounds >= 4 || 20 * ntile >= 17 * 256 * rounds;
+  if (pairs && work >= (1L << 17) && full && (work < (1L << 21) || (clov && a.nrhs > 1)))
     choice = a.nrhs > 1 && work >= (1L << 20) ? kPair2 : kPair1;
   // t-walks in t-chunk-major order: every XCD works on the same t-chunk, so the neighbour
   // re-reads that miss an XCD's L2 meet the chunk in the last-level cache (measured at
