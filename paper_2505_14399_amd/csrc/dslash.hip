@@ -448,11 +448,12 @@ __global__ __launch_bounds__(kBlock) void k_dslash_dir(const S* __restrict__ U, 
 template <class S>
 void launch_dir(const void* U, const void* in, void* out, const DslashArgs& a, hipStream_t st) {
   dim3 grid(unsigned((a.V + kBlock / 4 - 1) / (kBlock / 4)) * unsigned(a.nrhs));
-  // FP64 visits patches of 4 x 4 planes (16^3 x 32, one rhs: 30.2 -> 26.3 us; 24^3 x 64 106 -> 105); the
+  // FP64 visits patches of 4 x 4 planes (16^3 x 32, one rhs: 32.6 -> 27.4 us; 8 x 24 x 20 x 30 26.7 -> 25.0; 24^3 x 48 204
+  // -> 204), but not on lattices that the L2s hold anyway (8^3 x 16, 12 rhs: 16.8 -> 17.8); the
   // narrower types, whose planes are smaller against the L2, lose by it (BF16 16^3 x 32: 10.0 -> 11.8)
   auto patch = [](int L) { return L % 4 == 0 ? 4 : L % 2 == 0 ? 2 : 1; };
   const bool whole = (a.L[0] * a.L[1]) % (kBlock / 4) == 0;
-  const int bzt = whole && sizeof(S) == 16 ? patch(a.L[2]) | (patch(a.L[3]) << 8) : 0;
+  const int bzt = whole && sizeof(S) == 16 && a.V >= (1 << 15) ? patch(a.L[2]) | (patch(a.L[3]) << 8) : 0;
   auto go = [&](auto kern) { launch(kern, grid, dim3(kBlock), 0, st, U, in, out, a, bzt); };
   if (a.clov) {
     if (a.dagger) go(k_dslash_dir<S, true, true>);
