@@ -197,22 +197,17 @@ __global__ __launch_bounds__(256, sizeof(S) == 16 ? 2 : 1) void k_dslash_canon(c
   }
 }
 
-// One thread per site, for a single right-hand side of FP32 or 16-bit storage on lattices below 2^19
-// sites: there the passes through the LDS add latency that few waves hide (FP32, one right-hand
-// side, one thread per site against four directions: 16^3 x 32 16.3 against 20.6 us, 32^3 x 64 355
-// against 315 us; 16^3 x 32 with 4 rhs 57 against 50 us)
+// One thread per site and right-hand side; the rule stands at canon_site.
 template <class S, int MU, bool FWD, bool DAG>
 __device__ inline void site_hop(const S* __restrict__ U, const S* __restrict__ in, cplx<ctype<S>>* acc, int link_site,
-                                int nb_site, int V, ctype<S> coef) {
+                                int nb_site, int rhs, int V, ctype<S> coef) {
   using C = ctype<S>;
-  const S* ul = U + (size_t(MU) * V + link_site) * 9;
-  const S* p = in + size_t(nb_site) * 12;
   cplx<C> u[9], chi[12], h[6], w[6];
-#pragma unroll
-  for (int e = 0; e < 9; ++e) u[e] = ldc(ul, e);
   const C s = (FWD != DAG) ? C(-1) : C(1);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) chi[k] = ldc(p, k);
+  for (int e = 0; e < 9; ++e) u[e] = ldc(U, (size_t(MU) * V + link_site) * 9 + e);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) chi[k] = ldc(in, (size_t(rhs) * V + nb_site) * 12 + k);
   project<MU>(chi, s, h);
   su3_mul<C, !FWD>(u, h, w);
   reconstruct<MU>(acc, w, s, coef);
@@ -222,37 +217,97 @@ template <class S, bool DAG, bool CLOV>
 __global__ __launch_bounds__(256) void k_dslash_canon_site(const S* __restrict__ U, const S* __restrict__ in,
                                                            S* __restrict__ out, DslashArgs a) {
   using C = ctype<S>;
+  // the right-hand sides of a tile next to each other on one XCD: they share its links in the L2
+  const int wg = xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = wg / a.nrhs, rhs = wg - tile * a.nrhs;
+  const int site = tile * 256 + threadIdx.x;
   const int V = a.V;
-  const int site = xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (site >= V) return;
-  int rem = site, c[4], st[4];
-  for (int m = 0, s = 1; m < 4; ++m) {
-    c[m] = rem % a.L[m];
-    rem /= a.L[m];
-    st[m] = s;
-    s *= a.L[m];
+  const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2], L3 = a.L[3];
+  int rem = site;
+  const int x = rem % L0; rem /= L0;
+  const int y = rem % L1; rem /= L1;
+  const int z = rem % L2;
+  const int t = rem / L2;
+  const int s1 = L0, s2 = L0 * L1, s3 = L0 * L1 * L2;
+  const int xp = (x + 1 == L0) ? site - (L0 - 1) : site + 1;
+  const int xm = (x == 0) ? site + (L0 - 1) : site - 1;
+  const int yp = (y + 1 == L1) ? site - (L1 - 1) * s1 : site + s1;
+  const int ym = (y == 0) ? site + (L1 - 1) * s1 : site - s1;
+  const int zp = (z + 1 == L2) ? site - (L2 - 1) * s2 : site + s2;
+  const int zm = (z == 0) ? site + (L2 - 1) * s2 : site - s2;
+  const int tp = (t + 1 == L3) ? site - (L3 - 1) * s3 : site + s3;
+  const int tm = (t == 0) ? site + (L3 - 1) * s3 : site - s3;
+  C cw[4], diag;
+  if constexpr (sizeof(C) == 8) {
+    for (int m = 0; m < 4; ++m) cw[m] = a.cw_d[m];
+    diag = a.diag_d;
+  } else {
+    for (int m = 0; m < 4; ++m) cw[m] = a.cw_f[m];
+    diag = a.diag_f;
   }
-  auto fwd = [&](int m) { return c[m] + 1 == a.L[m] ? site - (a.L[m] - 1) * st[m] : site + st[m]; };
-  auto bwd = [&](int m) { return c[m] == 0 ? site + (a.L[m] - 1) * st[m] : site - st[m]; };
   const C mh = C(-0.5);
-  const C bt_f = (a.bc_t < 0 && c[3] == a.L[3] - 1) ? C(-1) : C(1), bt_b = (a.bc_t < 0 && c[3] == 0) ? C(-1) : C(1);
-  cplx<C> acc[1][12], v[1][12];
+  const C bt_f = (a.bc_t < 0 && t == L3 - 1) ? C(-1) : C(1), bt_b = (a.bc_t < 0 && t == 0) ? C(-1) : C(1);
+  cplx<C> acc[1][12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) acc[0][k] = {C(0), C(0)};
-  site_hop<S, 0, true, DAG>(U, in, acc[0], site, fwd(0), V, mh * a.cw_f[0]);
-  site_hop<S, 0, false, DAG>(U, in, acc[0], bwd(0), bwd(0), V, mh * a.cw_f[0]);
-  site_hop<S, 1, true, DAG>(U, in, acc[0], site, fwd(1), V, mh * a.cw_f[1]);
-  site_hop<S, 1, false, DAG>(U, in, acc[0], bwd(1), bwd(1), V, mh * a.cw_f[1]);
-  site_hop<S, 2, true, DAG>(U, in, acc[0], site, fwd(2), V, mh * a.cw_f[2]);
-  site_hop<S, 2, false, DAG>(U, in, acc[0], bwd(2), bwd(2), V, mh * a.cw_f[2]);
-  site_hop<S, 3, true, DAG>(U, in, acc[0], site, fwd(3), V, mh * a.cw_f[3] * bt_f);
-  site_hop<S, 3, false, DAG>(U, in, acc[0], bwd(3), bwd(3), V, mh * a.cw_f[3] * bt_b);
+  site_hop<S, 0, true, DAG>(U, in, acc[0], site, xp, rhs, V, mh * cw[0]);
+  site_hop<S, 0, false, DAG>(U, in, acc[0], xm, xm, rhs, V, mh * cw[0]);
+  site_hop<S, 1, true, DAG>(U, in, acc[0], site, yp, rhs, V, mh * cw[1]);
+  site_hop<S, 1, false, DAG>(U, in, acc[0], ym, ym, rhs, V, mh * cw[1]);
+  site_hop<S, 2, true, DAG>(U, in, acc[0], site, zp, rhs, V, mh * cw[2]);
+  site_hop<S, 2, false, DAG>(U, in, acc[0], zm, zm, rhs, V, mh * cw[2]);
+  site_hop<S, 3, true, DAG>(U, in, acc[0], site, tp, rhs, V, mh * cw[3] * bt_f);
+  site_hop<S, 3, false, DAG>(U, in, acc[0], tm, tm, rhs, V, mh * cw[3] * bt_b);
+  if constexpr (CLOV) {
+    cplx<C> v[1][12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[0][k] = ldc(in, size_t(site) * 12 + k);
-  if constexpr (CLOV) clover_acc<S, 1>(static_cast<const S*>(a.clov), site, V, v, acc);
+    for (int k = 0; k < 12; ++k) v[0][k] = ldc(in, (size_t(rhs) * V + site) * 12 + k);
+    clover_acc<S, 1>(static_cast<const S*>(a.clov), site, V, v, acc);
 #pragma unroll
-  for (int k = 0; k < 12; ++k)
-    stc(out, size_t(site) * 12 + k, CLOV ? acc[0][k] : C(a.diag_f) * v[0][k] + acc[0][k]);
+    for (int k = 0; k < 12; ++k) stc(out, (size_t(rhs) * V + site) * 12 + k, acc[0][k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const size_t i = (size_t(rhs) * V + site) * 12 + k;
+      cplx<C> v = ldc(in, i);
+      stc(out, i, diag * v + acc[0][k]);
+    }
+  }
+}
+
+// Where one thread per site and right-hand side is the faster form, us, that / four directions.  Four directions
+// pass everything through the LDS, which costs latency that few waves hide, and keep a tile's links over
+// several right-hand sides.  w: sites x right-hand sides.
+// FP32: a single right-hand side below 2^19 sites (16^3 x 32 16.4 / 20.6, 24^3 x 48 108 / 99); several for w
+// between 2^14 and 3 2^16 (10^3 x 16 with 2 6.8 / 7.4, 8^3 x 16 with 12 11.8 / 15.0, 10^3 x 16 with 12 21.4 / 28.7;
+// beyond 6^3 x 8 with 8 6.5 / 5.9, 15 x 17 x 19 x 21 with 2 30.1 / 27.4, 12^3 x 24 with 8 40.0 / 36.3), with the
+// site term up to 5 2^16 (12^3 x 24 with 5 32.6 / 34.6, 16^3 x 32 with 2 39.7 / 40.2, with 3 55.4 / 53.3).
+// FP16, whose site form needs 89 registers: a single one always (24^3 x 48 39 / 61), several for w between 2^15 and
+// 2^22 (12^3 x 24 with 2 8.7 / 11.2, 24^3 x 48 with 3 114 / 129; beyond 24^3 x 48 with 8 318 / 318).  BF16, whose
+// site form takes 256: never (16^3 x 32 with 1 16.5 / 16.0, 24^3 x 48 with 2 168 / 105).
+// FP64: four directions (16^3 x 32 48 / 38), but the site term spills beside the held links: with it a single one
+// from 2^15 sites (12^3 x 24 23.6 / 25.9, 24^3 x 48 371 / 392; 8^3 x 16 15.6 / 9.2), two on 2^17 sites or more (16^3 x 32
+// 101 / 107, 24^3 x 48 634 / 630), and several where the site form's workgroups nearly fill up to three rounds of the 256
+// CUs (12^3 x 16 with 2, 0.84 rounds, 24.0 / 28.8; 12^3 x 24 with 3, 1.9, 48.9 / 54.0; with 2, 1.3, 42.9 / 40.9; 14^3 x 28
+// with 3, 3.5, 94 / 85).
+template <class S>
+bool canon_site(const DslashArgs& a) {
+  const long w = long(a.V) * a.nrhs, one = 1;
+  switch (StoreTraits<S>::prec) {
+    case QMG_F64: {
+      if (!a.clov) return false;
+      if (a.nrhs == 1 ? w >= (one << 15) : a.nrhs == 2 && w >= (one << 18)) return true;
+      const long tiles = (w + 255) / 256, rounds = (tiles + 255) / 256;
+      return rounds <= 3 && tiles >= 256 * rounds - 90;
+    }
+    case QMG_F32:
+      return a.nrhs == 1 ? w < (one << 19) : w > (one << 14) && w < ((a.clov ? 5 : 3) * one << 16);
+    case QMG_F16:
+      return a.nrhs == 1 || (w > (one << 15) && w < (one << 22));
+    default:
+      return false;
+  }
 }
 
 template <class S>
@@ -260,14 +315,16 @@ void launch_canon(const S* U, const S* in, S* out, const DslashArgs& a, hipStrea
   const bool wide = size_t(a.V) * 12 * sizeof(S) >= (size_t(1) << 32);
   const int ntile = (a.V + kSites - 1) / kSites;
   // a group keeps its links over its right-hand sides; small lattices are cut into more groups, up
-  // to 2048 workgroups (16^3 x 32, 12 rhs FP64: 314 us with one group, 393 us with two)
-  const int ngroup = std::max(1, std::min(a.nrhs, 2048 / ntile));
+  // to 2048 workgroups, as even as they go (16^3 x 32, 12 rhs FP64: 316 us with one group, 393 us with two)
+  const int most = std::max(1, std::min(a.nrhs, 2048 / ntile)), per = (a.nrhs + most - 1) / most;
+  const int ngroup = (a.nrhs + per - 1) / per;
   const dim3 grid(unsigned(ntile) * unsigned(ngroup));
   auto go = [&](auto dag, auto clov) {
     constexpr bool D = decltype(dag)::value, CL = decltype(clov)::value;
-    if constexpr (sizeof(S) < 16) {
-      if (a.nrhs == 1 && a.V < (1 << 19)) {
-        launch(k_dslash_canon_site<S, D, CL>, dim3(unsigned((a.V + 255) / 256)), dim3(256), 0, st, U, in, out, a);
+    if constexpr (StoreTraits<S>::prec != QMG_BF16 && (sizeof(S) < 16 || CL)) {
+      if (canon_site<S>(a)) {
+        launch(k_dslash_canon_site<S, D, CL>, dim3(unsigned((a.V + 255) / 256) * unsigned(a.nrhs)), dim3(256), 0, st, U,
+               in, out, a);
         return;
       }
     }
