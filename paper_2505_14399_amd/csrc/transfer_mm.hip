@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void k_restrict_mm(const S* __restrict__ P, co
   S* pbuf = reinterpret_cast<S*>(smem);    // [k] columns of ROWS, stride PS
   S* buf = pbuf + size_t(a.k) * PS;        // [R][ROWS], stride PS
   // the aggregate's sites: looked up in memory inside fetch, a site would hold up the loads behind it
-  __shared__ int bs[kMmSites];
+  int* bs = reinterpret_cast<int*>(buf + size_t(min(8 * NT, a.nrhs)) * PS);
   for (int i = threadIdx.x; i < a.nd; i += 256) bs[i] = a.bsite[size_t(j) * a.nd + i];
   __syncthreads();
   const S* Pj = P + size_t(ja) * a.k * a.N;
@@ -362,7 +362,7 @@ void launch_restrict_mm(qmg_prec prec, const HierarchyDev& h, const void* P, con
       constexpr int NT = decltype(ntc)::value;
       const int G = 8 * NT;
       auto go = [&](auto kern, int MT) {
-        const size_t lds = std::max(size_t(h.k + std::min(G, nrhs)) * 104 * sizeof(S),
+        const size_t lds = std::max(size_t(h.k + std::min(G, nrhs)) * 104 * sizeof(S) + size_t(a.nd) * sizeof(int),
                                     size_t(3) * MT * NT * 256 * sizeof(double));
         if (lds > 64 * 1024)
           QMG_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
