@@ -113,7 +113,8 @@ void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const v
 void launch_restrict(qmg_prec prec, const HierarchyDev& h, const void* P, const void* fine, void* coarse, int nrhs,
                      hipStream_t st, bool canonical = false);
 // the same on the matrix cores (transfer_mm.hip), for the block shapes and counts that fit
-bool transfer_mm_fits(const HierarchyDev& h, int nrhs);
+bool prolong_mm_fits(qmg_prec prec, const HierarchyDev& h, int nrhs, bool canonical);
+bool restrict_mm_fits(qmg_prec prec, const HierarchyDev& h, int nrhs, bool canonical);
 void launch_prolong_mm(qmg_prec prec, const HierarchyDev& h, const void* P, const void* coarse, void* fine, int nrhs,
                        bool canonical, hipStream_t st);
 void launch_restrict_mm(qmg_prec prec, const HierarchyDev& h, const void* P, const void* fine, void* coarse, int nrhs,

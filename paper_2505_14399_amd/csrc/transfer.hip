@@ -959,7 +959,7 @@ void launch_prolong(qmg_prec prec, const HierarchyDev& h, const void* P, const v
   TimedLaunch tl("prolong", st, double(h.g.V) * (12.0 * h.k + 12.0 * nrhs) * prec_bytes(prec),
                  8.0 * 12.0 * h.k * h.g.V * nrhs);
   QMG_CHECK(h.k <= 64, QMG_EINVAL, "prolong: rank above 64");
-  if (transfer_mm_fits(h, nrhs)) return launch_prolong_mm(prec, h, P, coarse, fine, nrhs, canonical, st);
+  if (prolong_mm_fits(prec, h, nrhs, canonical)) return launch_prolong_mm(prec, h, P, coarse, fine, nrhs, canonical, st);
   dispatch_prec(prec, [&](auto tag) {
     using S = decltype(tag);
     constexpr int PK = kPack<S>;
@@ -996,7 +996,7 @@ void launch_restrict(qmg_prec prec, const HierarchyDev& h, const void* P, const 
                      hipStream_t st, bool canonical) {
   TimedLaunch tl("restrict", st, double(h.g.V) * (12.0 * h.k + 12.0 * nrhs) * prec_bytes(prec),
                  8.0 * 12.0 * h.k * h.g.V * nrhs);
-  if (transfer_mm_fits(h, nrhs)) return launch_restrict_mm(prec, h, P, fine, coarse, nrhs, canonical, st);
+  if (restrict_mm_fits(prec, h, nrhs, canonical)) return launch_restrict_mm(prec, h, P, fine, coarse, nrhs, canonical, st);
   dispatch_prec(prec, [&](auto tag) {
     using S = decltype(tag);
     constexpr int PK = kPack<S>;

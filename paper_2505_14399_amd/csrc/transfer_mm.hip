@@ -317,8 +317,28 @@ void by_nt(int nrhs, F&& f) {
 // faster one row pack per thread (transfer.hip): restrict / prolong at 16^3 x 32, rank 24, us, one
 // right-hand side FP32 56 / 57 against 77 / 69 here, FP64 119 / 115 against 144 / 123; four FP32
 // 112 / 94 against 80 / 70.
-bool transfer_mm_fits(const HierarchyDev& h, int nrhs) {
+static bool mm_shape(const HierarchyDev& h, int nrhs) {
   return nrhs > 1 && (h.blk.nd == 16 || h.blk.nd % 32 == 0) && h.blk.nd <= kMmSites && h.k <= 32;
+}
+
+// Native vectors need no packed copy, so up to four right-hand sides, which the row packs too take in one pass over P,
+// those are the faster on blocks of 32 sites or more where their threads fill the chip (rank 24, us, row packs /
+// here): FP32 from 2^18 sites (32^3 x 64 with 4 rhs 1380 / 1440, 24^3 x 48 with 2 344 / 382, 16^2 x 32^2 with 3 149 / 153;
+// 16^3 x 32 with 2 74 / 67), FP64 from 2^15 (24^4 with 4 340 / 370, 16^3 x 32 with 2 127 / 135; 8^3 x 16 10.4 / 9.6), and 16-bit
+// storage with two (16^3 x 32 40 / 43, with 4 56 / 50).  Blocks of 16 sites: 12^3 x 24, rank 12, FP32 with 4 25 / 19, BF16 with
+// 2 20 / 16, FP64 with 2 28.8 / 29.7, rank 8 22.3 / 20.4.
+bool prolong_mm_fits(qmg_prec prec, const HierarchyDev& h, int nrhs, bool canonical) {
+  if (!mm_shape(h, nrhs)) return false;
+  if (canonical || nrhs > 4) return true;
+  if (h.blk.nd == 16) return prec != QMG_F64 || nrhs > 2 || h.k <= 8;
+  if (prec == QMG_F64) return h.g.V < (1 << 15);
+  return prec == QMG_F32 ? h.g.V < (1 << 18) : nrhs > 2;
+}
+
+// In FP64 a workgroup of the few aggregates of a small lattice has more to do here than with groups of four (8^3 x 16,
+// rank 24, native, 5 rhs: row packs 52 us, here 56; 4 rhs 54 / 53).
+bool restrict_mm_fits(qmg_prec prec, const HierarchyDev& h, int nrhs, bool canonical) {
+  return mm_shape(h, nrhs) && (canonical || prec != QMG_F64 || nrhs <= 4 || h.blk.d >= 128);
 }
 
 void launch_prolong_mm(qmg_prec prec, const HierarchyDev& h, const void* P, const void* coarse, void* fine, int nrhs,
@@ -358,7 +378,9 @@ void launch_restrict_mm(qmg_prec prec, const HierarchyDev& h, const void* P, con
   a.nchunk = a.nd / 16;
   by_prec(prec, [&](auto tag) {
     using S = decltype(tag);
-    by_nt(nrhs, [&](auto ntc) {
+    // 16 right-hand sides a pass only where one pass fills the chip: with fewer than two workgroups a CU, passes of 8
+    // run beside each other (FP64, 8^3 x 16, rank 24, 12 rhs: 87.5 us in one pass, in two 55.7; row packs 71)
+    by_nt(a.d < 256 ? 8 : nrhs, [&](auto ntc) {
       constexpr int NT = decltype(ntc)::value;
       const int G = 8 * NT;
       auto go = [&](auto kern, int MT) {
