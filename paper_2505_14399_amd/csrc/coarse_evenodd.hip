@@ -372,7 +372,7 @@ void launch_coarse_eo_apply(qmg_prec prec, const HierarchyDev& h, int colour, co
              static_cast<const S*>(y), static_cast<const S*>(a), static_cast<const S*>(b), static_cast<S*>(out), list,
              nbh, dh, m, nrhs, H, lo, ns, sgn);
     };
-    if (coarse_mm_fits(h.k, nrhs)) {
+    if (coarse_mm_fits(prec, dh, h.k, nrhs)) {
       launch_coarse_mm<S>({B, y, a, b, out, list, nbh, sgn}, dh, h.k, nrhs, st);
       return;
     }

@@ -133,11 +133,23 @@ __global__ __launch_bounds__(64 * NQ * W, 4) void k_coarse_mm(
 // against 28.1 / 59.2 us; 8192 rows 270 / 364 against 376 / 604 us.
 constexpr int kCoarseMmRows = 2048;
 
-// Up to rank 24 the matrix cores are the faster from three right-hand sides on (512 rows, FP32, against a
-// thread per two rows and chunk of columns: rank 24 15.0 / 18.2 us, rank 20 13.3 / 14.1 us, rank 8 both at the
-// launch's 6.3 us), with a fourth tile of rows from five (256 rows, rank 32: 13.6 / 20.0 us; three right-hand
-// sides 16.8 / 16.7 us).
-bool coarse_mm_fits(int k, int nrhs) { return k <= 32 && nrhs >= (k <= 24 ? 3 : 5); }
+// Where the matrix cores are the faster, us, a thread per two rows and chunk of columns (groups of four right-hand
+// sides) / here.  Rows and columns are padded to tiles of 16, so that a fourth tile (ranks above 24) and, up to four
+// right-hand sides, ranks between the tiles lose: 2592 rows, three right-hand sides, FP32 rank 24 104 / 95, 22 81 / 89, 20
+// 74 / 78, 16 43 / 31, 10 28 / 25; FP64, whose matrix instructions run at the rate of its vector units, rank 24 239 / 186, 20
+// 133 / 162, 16 87 / 76, 12 48 / 44 (512 rows: 10.8 / 12.2), 8 32 / 18.  From five on the other form reads Y twice
+// (2592 rows, FP32 rank 20 138 / 79, FP64 rank 18 271 / 156), but groups of four on fewer rows than CUs run beside each
+// other (64 rows, 8 rhs, FP64 rank 18 8.8 / 12.1, rank 24 13.5 / 12.3, FP32 rank 18 7.3 / 7.9, rank 20 7.8 / 7.8; 32 rows, 12 rhs,
+// FP64 rank 24 11.9 / 12.2).
+bool coarse_mm_fits(qmg_prec prec, int d, int k, int nrhs) {
+  if (nrhs < 3 || k > 32) return false;
+  if (k <= 8) return true;
+  if (k > 24) return nrhs >= 5;
+  const bool f64 = prec == QMG_F64, crowd = long(d) * nrhs >= 1024;
+  if (nrhs >= 5) return k <= 16 || crowd || (!f64 && k >= 20) || (k == 24 && d >= 64);
+  if (f64) return k == 16 || (k == 24 && d >= 512);
+  return k <= 16 || k == 24 || (k >= 20 && d >= 128 && d < 1024);
+}
 
 template <class S>
 void launch_coarse_mm(const CoarseMm& c, int d, int k, int nrhs, hipStream_t st, const int* skip) {

@@ -135,7 +135,7 @@ struct CoarseMm {
   const int *list, *nb;
   double sgn;
 };
-bool coarse_mm_fits(int k, int nrhs);
+bool coarse_mm_fits(qmg_prec prec, int d, int k, int nrhs);
 template <class S>
 void launch_coarse_mm(const CoarseMm& c, int d, int k, int nrhs, hipStream_t st, const int* skip = nullptr);
 // third level: Philox coarse test vectors [n][d][m] FP64 (counter (j, g, v0 + n, level))

@@ -1051,7 +1051,7 @@ void launch_stencil_apply(qmg_prec prec, int d, int k, const int* cnb, const voi
       launch(kern, dim3(d, (nrhs + NR - 1) / NR), dim3(threads), uint32_t(lds), st, Y, in, out, cnb, d, m, nrhs, H,
              skip);
     };
-    if (coarse_mm_fits(k, nrhs)) {
+    if (coarse_mm_fits(prec, d, k, nrhs)) {
       launch_coarse_mm<S>({Y, nullptr, in, in, out, nullptr, cnb, 1.0}, d, k, nrhs, st, skip);
       return;
     }
