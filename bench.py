@@ -56,7 +56,7 @@ FAMILY_KERNEL = {
     "dslash/pair": ("k_dslash_pair<", "dslash_pair.hip"),
     "coarse_apply": ("k_coarse_mm<", "coarse_mm.hip"),  # of the batched solve's groups; one rhs: k_coarse_apply
     "restrict": ("k_restrict", "transfer_mm.hip"),
-    "prolong": ("k_prolong", "transfer_mm.hip"),
+    "prolong": ("k_prolong", "transfer.hip"),  # of the batched solve's groups of four native right-hand sides
     "coarse_build": ("k_build_coarse", "transfer.hip"),
     "evenodd/hop": ("k_hop_", "hop_pair.hip"),
     "coarse_eo": ("k_coarse_eo_apply", "coarse_evenodd.hip"),

@@ -553,13 +553,17 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
   // that many sites per thread along t, 16 = direction-split (four threads per site), 32/64 =
   // one site per thread for 2/4 right-hand sides at once (links loaded once for all of them),
   // 1000 z + 100 NR + TCH = t-walking with NR = 2 or 3 right-hand sides per thread (FP32; z:
-  // z-fastest tile order); 10000 + a t-walking code: the same in t-chunk-major workgroup order.  Default heuristic: for several right-hand sides in FP32 the
-  // multi-RHS t-walk (3 per thread when nrhs is a multiple of 3, else 2); otherwise the longest
-  // t-chunk that still gives >= 1024 workgroups, else the direction split when one thread per
-  // site would leave the GPU short of wavefronts.  With the autotuner enabled every valid
-  // variant is timed on first use of (precision, extents, nrhs, adjoint) and the fastest is
-  // kept.  With the clover term: forms 1, 16, 2, 4, 8 and the multi-RHS t-walks (FP32 and FP64
-  // storage), the direction split alone for BF16/FP16 storage.
+  // z-fastest tile order); 10000 + a t-walking code: the same in t-chunk-major workgroup order;
+  // kPair1 / kPair2 = two sites per thread for 1 or 2 right-hand sides (FP32; not offered as a forced variant).
+  // Default: BF16/FP16 storage the direction split.  Else the longest t-chunk that still gives >= 1024
+  // workgroups, or the direction split when one thread per site would leave the GPU short of wavefronts;
+  // in FP32 for several right-hand sides the multi-RHS t-walk (3 per thread when nrhs is a multiple of 3,
+  // else 2), but up to 2^19 sites x rhs the direction split; and over that, where rows are even, fields
+  // aligned and sites x rhs between 2^17 and 2^21 (with the clover term for several right-hand sides from
+  // 2^17 on), two sites per thread.  With the autotuner enabled every valid variant is timed on first use of
+  // (precision, extents, nrhs, adjoint) and the fastest is kept.  With the clover term: forms 1, 16, 2, 4,
+  // 8, the multi-RHS t-walks (FP32 and FP64 storage) and the pairs, the direction split alone for
+  // BF16/FP16 storage.
   const int Vs = a.L[0] * a.L[1] * a.L[2];
   const long wg1 = long((Vs + kBlock - 1) / kBlock) * a.nrhs;  // workgroups per t-slice
   const int Lt = a.L[3];
@@ -609,7 +613,7 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
     return;
   }
   auto fits = [&](int tch) { return Lt % tch == 0 && wg1 * (Lt / tch) >= 1024; };
-  // one thread per site fills 256 CUs x 32 wavefronts only from 2^18 sites x rhs on
+  // one thread per site fills 256 CUs x 32 wavefronts only from 2^19 sites x rhs on
   const bool small = long(a.V) * a.nrhs < (1L << 19);
   int choice = fits(8) ? 8 : fits(4) ? 4 : fits(2) ? 2 : small ? 16 : 1;
   // 4-byte storage (BF16/FP16): the one-thread-per-site forms hold every hop's loads in
@@ -623,16 +627,17 @@ void launch_s(const void* U, const void* in, void* out, const DslashArgs& a, hip
     const int z = (a.L[0] * a.L[1]) % kBlock == 0 ? 1 : 0;
     const int tch = (nr == 3 && Lt % 8 == 0) ? 8 : Lt % 4 == 0 ? 4 : 2;
     if (nr && valid(1000 * z + 100 * nr + tch)) choice = 1000 * z + 100 * nr + tch;
-    // too few sites for that: the direction split (clover, us, against the t-walk: 12^4 with 4 rhs 15.5 /
-    // 81, 12 rhs 35 / 107; 16^3 x 32 with 4 rhs 72 / 83, with 8 rhs 144 / 131)
+    // too few sites for that: the direction split (us, direction split / t-walk: Wilson on odd rows, which keep
+    // it, 15^3 x 16 with 2 rhs 14.0 / 44.7, 15 x 16^2 x 32 with 2 27 / 45, with 4 49.2 / 49.8, 25 x 24^2 x 18 with 2 58 / 74;
+    // clover 12^4 with 4 15.5 / 81, 12 rhs 35 / 107, 16^3 x 32 with 4 72 / 83, with 8 144 / 131)
     if (long(a.V) * a.nrhs <= (1L << 19)) choice = 16;
   }
   // Two sites per thread.  Against them the t-walks carry neighbours from step to step, and win where
   // there are sites enough (Wilson, us, t-walk / pairs: 32^3 x 64 with 1 rhs 261 / 276, 2 rhs 423 / 440;
   // 24^3 x 64 with 8 rhs 616 / 644; 24^3 x 48 with 4 rhs 264 / 261); below, and with the clover term for
-  // several right-hand sides everywhere, the pairs' 16-byte loads do (16^3 x 32 with 1 rhs 16.0 / 14.8, 4 rhs
-  // 47 / 37, 8 rhs 82 / 74, 12 rhs 127 / 105; 24^3 x 48 with 1 rhs 88 / 69; clover 16^3 x 32 with 4 rhs 83 / 49,
-  // 32^3 x 64 with 4 rhs 1186 / 937, 12 rhs 2994 / 2704, 1 rhs 413 / 420).  Below 2^17 sites x rhs half
+  // several right-hand sides everywhere, the pairs' 16-byte loads do (16^3 x 32 with 1 rhs 15.6 / 14.4, 4 rhs
+  // 47 / 36, 8 rhs 82 / 76, 12 rhs 127 / 107; 24^3 x 48 with 1 rhs 88 / 72; clover 16^3 x 32 with 4 rhs 83 / 46,
+  // 24^3 x 48 with 12 rhs 1068 / 814, 32^3 x 64 with 4 rhs 1196 / 947, 1 rhs 413 / 420).  Below 2^17 sites x rhs half
   // the threads are too few (18 x 5 x 9 x 13, 3 rhs: 9.0 / 10.0).
   const long work = long(a.V) * a.nrhs;
   // One right-hand side, against the direction split, whose workgroups are small: a last round of 512 sites to

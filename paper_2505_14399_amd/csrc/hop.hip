@@ -320,7 +320,8 @@ void launch_hop_eo(qmg_prec prec, const DslashArgs& a, const void* Ue, const voi
   // 12.3 against 21.3 us at 16^3 x 32).  Forced with the launch-variant codes 1 = one site per
   // thread, 16 = direction split.
   // The same holds for BF16/FP16 storage (BF16 at 16^3 x 32: Wilson 8.7 against 17.8 us, clover
-  // 21.0 against 18.5 us; the forms tie at 24^3 x 64).
+  // 21.0 against 18.5 us; the forms tie at 24^3 x 64).  FP32 from 2^18 sites x right-hand sides on goes to two sites per
+  // thread instead where rows allow (hop_pair.hip).
   const bool with_site_term = (ym == 2 && Ap) || (post == 1 && Aip);
   // FP32 without a forced variant: two sites per thread where its rule holds
   const bool pair = prec == QMG_F32 && a.tchunk == 0 && hop_pair_fits(a, Ue, Uo, in, y, out, Ap, Aip);

@@ -217,8 +217,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_hop_pair(const float2* __restrict
 }  // namespace
 
 // From 2^18 sites x right-hand sides on: below, half as many threads leave the chip short of waves
-// (two hops, us, one site per thread against two: 16^3 x 32 with 1 rhs 38 against 55, 2 rhs 51 / 48,
-// 4 rhs 88 / 60; 16^3 x 64 with 1 rhs 55 / 51; 24^3 x 48 with 1 rhs 128 / 105)
+// (two hops, us, one site per thread against two: 16^3 x 32 with 1 rhs 38 against 55, 2 rhs 50 / 44,
+// 4 rhs 72 / 57; 16^3 x 64 with 1 rhs 55 / 51; 24^3 x 48 with 1 rhs 129 / 103; with the site term, whose hops the
+// direction split took below 2^20: 16^3 x 32 with 2 rhs 62 / 51, 4 rhs 102 / 62, 24^3 x 48 with 1 rhs 170 / 148)
 bool hop_pair_fits(const DslashArgs& a, const void* Ue, const void* Uo, const void* in, const void* y,
                    const void* out, const void* Ap, const void* Aip) {
   uintptr_t bits = 0;

@@ -10,7 +10,8 @@
 // components of them together: their fine vectors pass through the LDS, so that the canonical layout
 // is read and written in whole runs of sites (96 bytes each in FP32) and needs no packed copy.
 // Measured at 32^3 x 64, rank 24, FP32, 12 right-hand sides on canonical vectors, against groups of
-// four with packed copies: prolong 5.5 -> 1.45 ms (5.0 TB/s of P and vectors), restrict 5.2 -> 1.76 ms.
+// four with packed copies: prolong 5.5 -> 1.45 ms (5.0 TB/s of P and vectors), restrict 5.2 -> 1.76 ms.  Where the
+// other form is the faster stands at prolong_mm_fits and restrict_mm_fits.
 // Relative error against 64 bits at 16^3 x 32: restrict 9.8e-8 -> 8.0e-8, prolong 9.7e-8 -> 7.5e-8.
 #include <algorithm>
 #include <type_traits>
