@@ -118,7 +118,8 @@ __device__ inline double sum_compensated(double p0, double p1, double p2, double
   add(p3);
   const double t = fma(d, o, s), b = t - s;
   e += (s - (t - b)) + fma(d, o, -b);
-  return t + e;
+  const double r = t + e;
+  return isfinite(r) ? r : t;  // an infinite sum has no rounding error: its e is not a number
 }
 
 // NE = 6: native links stored as their first two rows ([mu][6][V]); the third row of an SU(3)

@@ -85,3 +85,21 @@ def test_diagonal_term_is_rounded_once(qmg, layout, prec, dag):
         got = to_np(op(lat, to_gpu(U.astype(t)), to_gpu(psi.astype(t))))
     ref = wilson.apply_wilson(U.astype(np.clongdouble), psi.astype(np.clongdouble), m, xi, -1, dims, dagger=dag)
     assert rel(got.astype(np.clongdouble), ref) < ONCE * u
+
+
+# sums beyond the largest number are infinite, not undefined: hops below it, diagonal term above
+@pytest.mark.parametrize("layout", ["canonical", "native"])
+@pytest.mark.parametrize("prec,big", [("f64", 1e307), ("f32", 1e37)])
+def test_overflow_stays_infinite(qmg, layout, prec, big):
+    dims = (5, 6, 4, 8)
+    banner(f"overflow of the diagonal term {dims} {prec} {layout}")
+    U = fields.random_gauge(dims, 0.6, 5)
+    psi = torch.full((3, int(np.prod(dims)), 4, 3), big, dtype=torch.complex128, device="cuda")
+    lat = qmg.Lattice(dims, 50.5, 2.0, -1)
+    if layout == "native":
+        u, p = qmg.pack_gauge(lat, to_gpu(U), prec), qmg.pack_spinor(lat, psi, prec)
+        got = qmg.unpack_spinor(lat, qmg.wilson_apply(lat, u, p, layout="native"), prec)
+    else:
+        t = torch.complex128 if prec == "f64" else torch.complex64
+        got = qmg.wilson_apply(lat, to_gpu(U).to(t), psi.to(t))
+    assert torch.all(got.real == float("inf")) and torch.all(torch.isfinite(got.imag))
