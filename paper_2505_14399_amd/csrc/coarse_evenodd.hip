@@ -135,8 +135,8 @@ __global__ __launch_bounds__(256) void k_coarse_eo_blocks(const double2* __restr
   if (tid == 0) atomicMax(reinterpret_cast<unsigned long long*>(flag + 2), omax);
 }
 
-// One colour of the even-odd coarse operator (the form in the file header) on few right-hand sides (more
-// go to the matrix cores).  One workgroup per
+// One colour of the even-odd coarse operator (the form in the file header) on one or two right-hand
+// sides, and on more where the matrix cores lose (coarse_mm_fits).  One workgroup per
 // (aggregate of the colour, group of NR right-hand sides); the staged inputs and the column
 // chunking over H follow the full coarse apply: thread (h, slot, row pack) forms PR rows of
 // B_slot(j) times its input over column chunk h, the partial rows are summed in LDS.  Slots

@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void k_restrict(const S* __restrict__ P, const
   }
 }
 
-// coarse apply on one or two right-hand sides (four above rank 24; more go to the matrix cores): one
+// coarse apply on one or two right-hand sides, and on more where the matrix cores lose (coarse_mm_fits): one
 // workgroup per (aggregate, group of NR right-hand sides).  The nine input
 // vectors v(j + slot) are staged in LDS.  Thread (h, slot, row pack) forms PR rows of
 // Y_slot(j) times v(j + slot) over column chunk h of H (each Y entry read once per group of
